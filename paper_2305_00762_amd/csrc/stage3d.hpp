@@ -71,42 +71,9 @@ __device__ __forceinline__ void conv_flux3(const double W[5], double g1inv, doub
   F[4] = W[1] * (E + W[4]);
 }
 
-// HLLC with Einfeldt (Roe-average) bounds in the wave-sum form, both
-// tangential momenta carried by the star states (as the 2D hllc).
 __device__ __forceinline__ void hllc3(const double WL[5], const double WR[5], const double Fm[5],
                                       double gamma, double g1inv, double F[5]) {
-  const double rl = WL[0], ul = WL[1], vl = WL[2], wl = WL[3], pl = WL[4];
-  const double rr = WR[0], ur = WR[1], vr = WR[2], wr = WR[3], pr = WR[4];
-  const double yl = rsq_nr(rl), yr = rsq_nr(rr);
-  const double sl = rl * yl, sr = rr * yr;
-  const double irl = yl * yl, irr = yr * yr;
-  const double El = pl * g1inv + 0.5 * rl * (ul * ul + vl * vl + wl * wl);
-  const double Er = pr * g1inv + 0.5 * rr * (ur * ur + vr * vr + wr * wr);
-  const double cl = sqrt_nr(gamma * pl * irl), cr = sqrt_nr(gamma * pr * irr);
-  const double hl = (El + pl) * irl, hr = (Er + pr) * irr;
-  const double iss = rcp_nr(sl + sr);
-  const double ut = (sl * ul + sr * ur) * iss;
-  const double vt = (sl * vl + sr * vr) * iss;
-  const double wt = (sl * wl + sr * wr) * iss;
-  const double ht = (sl * hl + sr * hr) * iss;
-  const double ct = sqrt_nr((gamma - 1.0) * (ht - 0.5 * (ut * ut + vt * vt + wt * wt)));
-  const double SL = fmin(ul - cl, ut - ct);
-  const double SR = fmax(ur + cr, ut + ct);
-  const double ml = rl * (SL - ul), mr = rr * (SR - ur);
-  const double Ss = (pr - pl + ml * ul - mr * ur) * rcp_nr(ml - mr);
-  const double kl = ml * rcp_nr(SL - Ss), kr = mr * rcp_nr(SR - Ss);
-  const double QL[5] = {rl, rl * ul, rl * vl, rl * wl, El};
-  const double QR[5] = {rr, rr * ur, rr * vr, rr * wr, Er};
-  const double QsL[5] = {kl, kl * Ss, kl * vl, kl * wl,
-                         kl * (El * irl + (Ss - ul) * (Ss + pl * rcp_nr(ml)))};
-  const double QsR[5] = {kr, kr * Ss, kr * vr, kr * wr,
-                         kr * (Er * irr + (Ss - ur) * (Ss + pr * rcp_nr(mr)))};
-  const double aL = fabs(SL), aS = fabs(Ss), aR = fabs(SR);
-#pragma unroll
-  for (int m = 0; m < 5; ++m) {
-    const double diss = aL * (QsL[m] - QL[m]) + aS * (QsR[m] - QsL[m]) + aR * (QR[m] - QsR[m]);
-    F[m] = Fm[m] - 0.5 * diss;
-  }
+  hllc_n<5>(WL, WR, Fm, 1.0, gamma, g1inv, F);
 }
 
 // Characteristic MEG7 states in 3D: the primitive eigenvectors of the 2D
