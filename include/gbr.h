@@ -101,8 +101,9 @@ int gbr_set_geometry(gbr_ctx *ctx, double x0, double x1, double y0, double y1,
  * interface, while smooth interfaces keep the reconstructed cell fluxes of
  * eqs. flux-full, flux-right; FP64, plain detector, seventh order, HLLC, on
  * the 31x15 and 15x15 tilings), precision = GBR_PREC_FP64
- * or GBR_PREC_FP32_BULK (gradients, reconstruction and fluxes in float32 with
- * FP64 state, stage update and flux differencing), detector = GBR_DET_PLAIN
+ * or GBR_PREC_FP32_BULK (GRB reconstruction and Riemann solver in float32 on
+ * local jumps, with FP64 state, mean fluxes, stage update and flux
+ * differencing), detector = GBR_DET_PLAIN
  * (density detector, Sec. 2.4) or GBR_DET_MLP (learned detector, needs
  * gbr_mlp_set_weights).  Unsupported combinations return GBR_EUNSUPPORTED
  * and leave the scheme unchanged. */
@@ -230,8 +231,8 @@ int gbr_get_flags(gbr_ctx *ctx, uint8_t *sig_x, uint8_t *sig_y, void *stream);
 int gbr_timing(gbr_ctx *ctx, int enable);
 int gbr_timing_read(gbr_ctx *ctx, double *detector_ms, double *stage_ms, uint64_t *launches);
 
-/* Tile shapes of the stage kernel.  gbr_tiling_count() is the number of
- * compiled shapes; gbr_set_tiling selects one (0 = default 31x15 cells per
+/* Tile shapes of the stage kernel (31x15, 15x15, 63x7, 30x15, 15x7).
+ * gbr_tiling_count() is the number of compiled shapes; gbr_set_tiling selects one (0 = default 31x15 cells per
  * workgroup); gbr_get_tiling reports the shape in use (the viscous form falls
  * back to variant 0 where a shape has no viscous build).  gbr_autotune times
  * every shape on the residual of the device state Q (reps launches each,

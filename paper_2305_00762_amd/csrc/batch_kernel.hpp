@@ -18,10 +18,7 @@
 // workgroup leaves the tile loop after at most ceil(total / gridDim.x)
 // rounds.
 #pragma once
-#include <type_traits>
-
-#include "dt_kernel.hpp"
-#include "stage_f32.hpp"
+#include "stage_line.hpp"
 
 namespace gbr {
 
@@ -57,39 +54,15 @@ __device__ __forceinline__ int batch_find(const int* ts, int n, int t) {
   return lo;
 }
 
-constexpr int imax(int a, int b) { return a > b ? a : b; }
-constexpr int imin(int a, int b) { return a < b ? a : b; }
-
-// MW: waves per SIMD the register budget must allow (the tile loop would
-// otherwise let the compiler spend the budget of the smaller of the two forms).
-template <class CI, class CV, bool F32, int MW>
-struct BatchCfg {
-  static_assert(CI::TX == CV::TX && CI::TY == CV::TY && CI::NT == CV::NT, "one tile shape");
-  static constexpr int TX = CI::TX, TY = CI::TY, NT = CI::NT;
-  static constexpr int MINW = MW;
-  // the FP64 tiles take the edge form (primitive MEG7, MP test where flagged)
-  using LI = typename CI::template Layout<true>;
-  using LV = typename CV::template Layout<true>;
-  static constexpr int U = F32 ? imax(F32Cfg<CI>::NU * CI::RS, F32Cfg<CV>::NU * CV::RS)
-                                : imax(LI::NFU * CI::RS, LV::NFU * CV::RS);
-  static constexpr int PH = F32 ? imax(F32Cfg<CI>::PH, F32Cfg<CV>::PH) : imax(LI::PH, LV::PH);
-  static constexpr int CHI = F32 ? imax(F32Cfg<CI>::CHI, F32Cfg<CV>::CHI) : imax(CI::CHI, CV::CHI);
-  static constexpr int QMAX = imax(CI::QMAX, CV::QMAX);
-  using PhT = typename std::conditional<F32, float, double>::type;
-  // queue entries: bytes where every slot fits (FP32 form), else 16 bits
-  using QT = typename std::conditional<(F32 && QMAX <= 256), unsigned char, unsigned short>::type;
-  static constexpr int LDS_BYTES = 8 * U + (int)sizeof(PhT) * PH + CHI + (int)sizeof(QT) * QMAX + 16;
-};
-
-template <class CI, class CV, bool F32, int MW, bool LOOP>
-__global__ __launch_bounds__(CI::NT, MW) void meg7_batch_kernel(BatchParams B) {
-  using BC = BatchCfg<CI, CV, F32, MW>;
-  using PhT = typename BC::PhT;
-  __shared__ double sU[BC::U];
-  __shared__ PhT sPh[BC::PH];
-  __shared__ unsigned char sChi[BC::CHI];
-  __shared__ typename BC::QT sQueue[BC::QMAX];
-  __shared__ int sQCount;
+// CI, CV: the inviscid and the viscous form of one tile shape (same lanes per
+// line, so the same workgroup); F32 as in the single-grid kernel.
+template <class CI, class CV, bool F32, bool LOOP>
+__global__ __launch_bounds__(CI::NT, CI::MINW) void meg7_batch_kernel(BatchParams B) {
+  static_assert(CI::TX == CV::TX && CI::TY == CV::TY && CI::NT == CV::NT && CI::RS == CV::RS &&
+                    CI::QN == CV::QN,
+                "one tile shape");
+  __shared__ double sU[4 * CI::RS];
+  __shared__ typename CI::QT sQueue[CI::QN];
   const int G = gridDim.x, b = blockIdx.x;
   const int xcd = b & 7, per = G >> 3;   // G is a multiple of 8
   for (int base = 0; base < B.total; base += G) {
@@ -98,65 +71,15 @@ __global__ __launch_bounds__(CI::NT, MW) void meg7_batch_kernel(BatchParams B) {
       const int p = batch_find(B.tile_start, B.nprob, t);
       const StageParams& P = B.tab[p];
       const int lt = t - B.tile_start[p];
-      const int tx0 = (lt % P.tiles_x) * BC::TX, ty0 = (lt / P.tiles_x) * BC::TY;
-      if constexpr (F32) {
-        if (P.mu > 0.0)
-          stage_tile_f32<CV, false>(P, tx0, ty0, sU, sPh, sChi, sQueue, &sQCount, nullptr);
-        else
-          stage_tile_f32<CI, false>(P, tx0, ty0, sU, sPh, sChi, sQueue, &sQCount, nullptr);
-      } else {
-        if (P.mu > 0.0)
-          stage_tile<CV, false>(P, tx0, ty0, sU, sPh, sChi, sQueue, &sQCount, nullptr);
-        else
-          stage_tile<CI, false>(P, tx0, ty0, sU, sPh, sChi, sQueue, &sQCount, nullptr);
-      }
+      const int tx0 = (lt % P.tiles_x) * CI::TX, ty0 = (lt / P.tiles_x) * CI::TY;
+      if (P.mu > 0.0)
+        stage_tile_line<CV, false, false, 7, false, F32>(P, tx0, ty0, sU, sQueue, nullptr);
+      else
+        stage_tile_line<CI, false, false, 7, false, F32>(P, tx0, ty0, sU, sQueue, nullptr);
     }
     if (!LOOP) break;   // one tile per workgroup: gridDim.x >= total
     __syncthreads();
   }
-}
-
-// ---------------------------------------------------------------------------
-// Per-grid time step: kBatchDtBlocks partial minima per grid, then one thread
-// per grid folds them (a min is exact: the result equals the single-grid one).
-constexpr int kBatchDtBlocks = 32;
-
-__global__ __launch_bounds__(kDtThreads) void batch_dt_reduce_kernel(const BatchProb* prob, int qn,
-                                                                     double* partial,
-                                                                     unsigned* status) {
-  __shared__ double red[kDtThreads / 64];
-  const int p = blockIdx.x / kBatchDtBlocks, k = blockIdx.x % kBatchDtBlocks;
-  const BatchProb& g = prob[p];
-  const double* Q = g.buf[qn];
-  const size_t n = (size_t)g.nx * g.ny;
-  double conv = __builtin_inf(), visc = __builtin_inf();
-  bool bad = false;
-  for (size_t s = (size_t)k * kDtThreads + threadIdx.x; s < n;
-       s += (size_t)kBatchDtBlocks * kDtThreads)
-    dt_cell(Q, n, s, g.gamma, g.mu, g.dx, g.dy, conv, visc, bad);
-  if (bad) atomicOr(status, 1u);
-  conv = block_min(conv, red);
-  visc = block_min(visc, red);
-  if (threadIdx.x == 0) {
-    partial[(size_t)p * 2 * kBatchDtBlocks + k] = conv;
-    partial[(size_t)p * 2 * kBatchDtBlocks + kBatchDtBlocks + k] = visc;
-  }
-}
-
-__global__ __launch_bounds__(256) void batch_dt_finish_kernel(const BatchProb* prob, int nprob,
-                                                              const double* partial, double* dt,
-                                                              unsigned* status) {
-#pragma clang fp contract(off)
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= nprob) return;
-  double conv = __builtin_inf(), visc = __builtin_inf();
-  for (int k = 0; k < kBatchDtBlocks; ++k) {
-    conv = fmin(conv, partial[(size_t)p * 2 * kBatchDtBlocks + k]);
-    visc = fmin(visc, partial[(size_t)p * 2 * kBatchDtBlocks + kBatchDtBlocks + k]);
-  }
-  const double d = prob[p].cfl * fmin(visc / kAlphaV, conv);
-  dt[p] = d;
-  if (!(d > 0.0) || !isfinite(d)) atomicOr(status, 2u);
 }
 
 }  // namespace gbr

@@ -9,6 +9,7 @@
 // atomics are used.  A bad cell (non-finite, rho <= 0, p <= 0) is recorded
 // in the status word, since fmin would otherwise drop a NaN.
 #pragma once
+#include "batch_kernel.hpp"
 #include "stage_kernel.hpp"
 
 namespace gbr {
@@ -261,6 +262,49 @@ __global__ __launch_bounds__(256) void div_selftest_kernel(unsigned long long se
 // t += dt on the device (the clock of moving boundary segments).
 __global__ void advance_time_kernel(double* t, const double* dt) {
   if (threadIdx.x == 0) *t = *t + *dt;
+}
+
+// ---------------------------------------------------------------------------
+// Per-grid time step: kBatchDtBlocks partial minima per grid, then one thread
+// per grid folds them (a min is exact: the result equals the single-grid one).
+constexpr int kBatchDtBlocks = 32;
+
+__global__ __launch_bounds__(kDtThreads) void batch_dt_reduce_kernel(const BatchProb* prob, int qn,
+                                                                     double* partial,
+                                                                     unsigned* status) {
+  __shared__ double red[kDtThreads / 64];
+  const int p = blockIdx.x / kBatchDtBlocks, k = blockIdx.x % kBatchDtBlocks;
+  const BatchProb& g = prob[p];
+  const double* Q = g.buf[qn];
+  const size_t n = (size_t)g.nx * g.ny;
+  double conv = __builtin_inf(), visc = __builtin_inf();
+  bool bad = false;
+  for (size_t s = (size_t)k * kDtThreads + threadIdx.x; s < n;
+       s += (size_t)kBatchDtBlocks * kDtThreads)
+    dt_cell(Q, n, s, g.gamma, g.mu, g.dx, g.dy, conv, visc, bad);
+  if (bad) atomicOr(status, 1u);
+  conv = block_min(conv, red);
+  visc = block_min(visc, red);
+  if (threadIdx.x == 0) {
+    partial[(size_t)p * 2 * kBatchDtBlocks + k] = conv;
+    partial[(size_t)p * 2 * kBatchDtBlocks + kBatchDtBlocks + k] = visc;
+  }
+}
+
+__global__ __launch_bounds__(256) void batch_dt_finish_kernel(const BatchProb* prob, int nprob,
+                                                              const double* partial, double* dt,
+                                                              unsigned* status) {
+#pragma clang fp contract(off)
+  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= nprob) return;
+  double conv = __builtin_inf(), visc = __builtin_inf();
+  for (int k = 0; k < kBatchDtBlocks; ++k) {
+    conv = fmin(conv, partial[(size_t)p * 2 * kBatchDtBlocks + k]);
+    visc = fmin(visc, partial[(size_t)p * 2 * kBatchDtBlocks + kBatchDtBlocks + k]);
+  }
+  const double d = prob[p].cfl * fmin(visc / kAlphaV, conv);
+  dt[p] = d;
+  if (!(d > 0.0) || !isfinite(d)) atomicOr(status, 2u);
 }
 
 }  // namespace gbr

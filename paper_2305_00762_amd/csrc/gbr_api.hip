@@ -13,149 +13,11 @@
 #include "dt_kernel.hpp"
 #include "mlp_kernels.hpp"
 #include "stage3d.hpp"
-#include "stage_f32.hpp"
-#include "stage_kernel.hpp"
+#include "stage_variants.hpp"
 
 namespace {
 
 using namespace gbr;
-
-// Threads per workgroup of every single-grid stage kernel: a stage-3 launch
-// leaves one time-step slot per wave, kStageThreads / 64 per tile.
-constexpr int kStageThreads = 256;
-constexpr int kStageWaves = kStageThreads / 64;
-
-template <class C, bool MLP = false, bool CONS = false, int ORD = 7, bool LM = false,
-          bool MPE = false>
-void launch_cfg(const StageParams& P, hipStream_t s) {
-  static_assert(C::LDS_BYTES <= 160 * 1024, "LDS per workgroup");
-  static_assert(C::NT == kStageThreads, "time-step slots assume kStageThreads per workgroup");
-  hipLaunchKernelGGL((meg7_stage_kernel<C, MLP, CONS, ORD, LM, MPE>), dim3(P.ntiles), dim3(C::NT),
-                     0, s, P);
-}
-template <class C, bool MLP = false>
-void launch_cfg_f32(const StageParams& P, hipStream_t s) {
-  static_assert(F32Cfg<C>::LDS_BYTES <= 160 * 1024, "LDS per workgroup");
-  static_assert(C::NT == kStageThreads, "time-step slots assume kStageThreads per workgroup");
-  hipLaunchKernelGGL((meg7_stage_kernel_f32<C, MLP>), dim3(P.ntiles), dim3(C::NT), 0, s, P);
-}
-using LaunchFn = void (*)(const StageParams&, hipStream_t);
-
-// Tile shapes of the stage kernel: TX x TY cells per workgroup, x sweep in
-// sub-blocks of SX rows, y sweep in sub-blocks of SY columns, 256 threads.
-// Shapes trade halo recomputation (small tiles) against LDS per workgroup
-// (workgroups per CU); gbr_autotune times them on the caller's state.
-struct TileVariant {
-  int tx, ty;
-  LaunchFn fn[2][2][2];   // [precision FP64/FP32-bulk][viscous][learned detector]; null: no build
-  const char* name;
-  LaunchFn cons[2];       // MEG7-cons, FP64 with the plain detector: [viscous]; null: no build
-  LaunchFn g4[2][2];      // fourth-order GRB, FP64 with the plain detector: [cons][viscous]
-  LaunchFn ss[2][2];      // shock-stable HLLC, seventh order, FP64, plain: [cons][viscous]
-  LaunchFn mpe[2][2];     // MP test at every interface, seventh order, FP64, plain: [cons][viscous]
-};
-using E31 = TileCfg<31, 15, 15, 16, 256, false>;
-using V31 = TileCfg<31, 15, 8, 16, 256, true>;
-// FP64 on 15x15 tiles: 3 workgroups per CU fit the LDS, so the register
-// budget is held to 3 waves per SIMD (168 VGPRs)
-using E15 = TileCfg<15, 15, 15, 15, 256, false, 3>;
-using V15 = TileCfg<15, 15, 15, 15, 256, true, 3>;
-// FP32 bulk on 15x15 tiles: 4 workgroups per CU fit the LDS, so the register
-// budget is held to 4 waves per SIMD (128 VGPRs)
-using F15 = TileCfg<15, 15, 15, 15, 256, false, 4>;
-using FV15 = TileCfg<15, 15, 15, 15, 256, true, 4>;
-const TileVariant kVariants[] = {
-    // 32 x-interfaces per row, 16 y-interfaces per column; 2 workgroups/CU
-    {31, 15,
-     {{{launch_cfg<E31>, launch_cfg<E31, true>}, {launch_cfg<V31>, launch_cfg<V31, true>}},
-      {{launch_cfg_f32<E31>, launch_cfg_f32<E31, true>},
-       {launch_cfg_f32<V31>, launch_cfg_f32<V31, true>}}},
-     "31x15",
-     {launch_cfg<E31, false, true>, launch_cfg<V31, false, true>},
-     {{launch_cfg<E31, false, false, 4>, launch_cfg<V31, false, false, 4>},
-      {launch_cfg<E31, false, true, 4>, launch_cfg<V31, false, true, 4>}},
-     {{launch_cfg<E31, false, false, 7, true>, launch_cfg<V31, false, false, 7, true>},
-      {launch_cfg<E31, false, true, 7, true>, launch_cfg<V31, false, true, 7, true>}},
-     {{launch_cfg<E31, false, false, 7, false, true>, launch_cfg<V31, false, false, 7, false, true>},
-      {launch_cfg<E31, false, true, 7, false, true>, launch_cfg<V31, false, true, 7, false, true>}}},
-    // 16 interfaces per line both ways; 3-4 workgroups/CU
-    {15, 15,
-     {{{launch_cfg<E15>, launch_cfg<E15, true>}, {launch_cfg<V15>, launch_cfg<V15, true>}},
-      {{launch_cfg_f32<F15>, launch_cfg_f32<F15, true>},
-       {launch_cfg_f32<FV15>, launch_cfg_f32<FV15, true>}}},
-     "15x15",
-     {launch_cfg<E15, false, true>, launch_cfg<V15, false, true>},
-     {{launch_cfg<E15, false, false, 4>, launch_cfg<V15, false, false, 4>},
-      {launch_cfg<E15, false, true, 4>, launch_cfg<V15, false, true, 4>}},
-     {{launch_cfg<E15, false, false, 7, true>, launch_cfg<V15, false, false, 7, true>},
-      {launch_cfg<E15, false, true, 7, true>, launch_cfg<V15, false, true, 7, true>}},
-     {{launch_cfg<E15, false, false, 7, false, true>, launch_cfg<V15, false, false, 7, false, true>},
-      {launch_cfg<E15, false, true, 7, false, true>, launch_cfg<V15, false, true, 7, false, true>}}},
-    // 64 x-interfaces per row, 8 y-interfaces per column (Euler, plain detector)
-    {63, 7,
-     {{{launch_cfg<TileCfg<63, 7, 7, 32, 256, false>>,
-        launch_cfg<TileCfg<63, 7, 7, 32, 256, false>, true>},
-       {nullptr, nullptr}},
-      {{launch_cfg_f32<TileCfg<63, 7, 7, 32, 256, false>>,
-        launch_cfg_f32<TileCfg<63, 7, 7, 32, 256, false>, true>},
-       {nullptr, nullptr}}},
-     "63x7",
-     {nullptr, nullptr},
-     {{nullptr, nullptr}, {nullptr, nullptr}},
-     {{nullptr, nullptr}, {nullptr, nullptr}},
-     {{nullptr, nullptr}, {nullptr, nullptr}}},
-    // 31x8 / 15x16 interface blocks sized for 3 workgroups per CU in FP32 bulk
-    {30, 15,
-     {{{launch_cfg<TileCfg<30, 15, 15, 15, 256, false>>,
-        launch_cfg<TileCfg<30, 15, 15, 15, 256, false>, true>},
-       {nullptr, nullptr}},
-      {{launch_cfg_f32<TileCfg<30, 15, 8, 15, 256, false, 3>>,
-        launch_cfg_f32<TileCfg<30, 15, 8, 15, 256, false, 3>, true>},
-       {nullptr, nullptr}}},
-     "30x15",
-     {nullptr, nullptr},
-     {{nullptr, nullptr}, {nullptr, nullptr}},
-     {{nullptr, nullptr}, {nullptr, nullptr}},
-     {{nullptr, nullptr}, {nullptr, nullptr}}},
-};
-constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
-
-// Forms of the batched kernel: tile shape (inviscid and viscous forms of one
-// shape) x persistent tile loop or one workgroup per tile.
-template <class CI, class CV, bool F32, int MW, bool LOOP>
-void launch_batch(const BatchParams& B, int grid, hipStream_t s) {
-  static_assert(BatchCfg<CI, CV, F32, MW>::LDS_BYTES <= 160 * 1024, "LDS per workgroup");
-  hipLaunchKernelGGL((meg7_batch_kernel<CI, CV, F32, MW, LOOP>), dim3(grid), dim3(CI::NT), 0, s, B);
-}
-template <class CI, class CV, bool F32, int MW, bool LOOP>
-int batch_blocks_per_cu() {
-  int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, meg7_batch_kernel<CI, CV, F32, MW, LOOP>,
-                                                    CI::NT, 0) != hipSuccess)
-    return 0;
-  return n;
-}
-using BatchLaunchFn = void (*)(const BatchParams&, int, hipStream_t);
-struct BatchVariant {
-  int tx, ty, loop;
-  BatchLaunchFn fn[2];   // [FP64, FP32 bulk]
-  int (*occ[2])();
-  const char* name;
-};
-#define GBR_BATCH_VARIANT(TX, TY, CI, CV, MW64, MW32, LOOP, NAME)                     \
-  {TX, TY, LOOP,                                                                      \
-   {launch_batch<CI, CV, false, MW64, LOOP>, launch_batch<CI, CV, true, MW32, LOOP>}, \
-   {batch_blocks_per_cu<CI, CV, false, MW64, LOOP>,                                   \
-    batch_blocks_per_cu<CI, CV, true, MW32, LOOP>},                                   \
-   NAME}
-const BatchVariant kBatchVariants[] = {
-    GBR_BATCH_VARIANT(31, 15, E31, V31, 2, 2, true, "31x15 persistent"),
-    GBR_BATCH_VARIANT(15, 15, E15, V15, 3, 2, true, "15x15 persistent"),
-    GBR_BATCH_VARIANT(31, 15, E31, V31, 2, 2, false, "31x15 one tile per workgroup"),
-    GBR_BATCH_VARIANT(15, 15, E15, V15, 2, 4, false, "15x15 one tile per workgroup"),
-};
-#undef GBR_BATCH_VARIANT
-constexpr int kNumBatchVariants = sizeof(kBatchVariants) / sizeof(kBatchVariants[0]);
 
 }  // namespace
 
@@ -179,7 +41,7 @@ struct gbr_ctx {
   int stage3_slots;           // slots of the last stage-3 call; 0: none since gbr_stage_dt
   uint8_t* d_sigx;
   uint8_t* d_sigy;
-  int tiling;                 // index into kVariants
+  int tiling;                 // index into tile_variants()
   // learned detector: inference image (bf16 W1, W2; float w3, biases)
   unsigned short* d_mlp_w;    // [2][32][32]
   float* d_mlp_f;             // [32 + 65]
@@ -289,8 +151,8 @@ int gbr_init(int nx, int ny, double gamma, double mu, double Pr, gbr_ctx** out) 
   // the smallest tile shape
   c->dtx_cap = 0;
   for (int v = 0; v < kNumVariants; ++v) {
-    const int t = ((nx + kVariants[v].tx - 1) / kVariants[v].tx) *
-                  ((ny + kVariants[v].ty - 1) / kVariants[v].ty) * kStageWaves;
+    const int t = ((nx + tile_variants()[v].tx - 1) / tile_variants()[v].tx) *
+                  ((ny + tile_variants()[v].ty - 1) / tile_variants()[v].ty) * kMaxStageWaves;
     c->dtx_cap = t > c->dtx_cap ? t : c->dtx_cap;
   }
   if (hipMalloc(&c->d_dtx, 3 * (size_t)c->dtx_cap * sizeof(double)) != hipSuccess) {
@@ -468,14 +330,14 @@ int gbr_check(gbr_ctx* c, void* stream) {
 static LaunchFn variant_fn(const gbr_ctx* c, int v) {
   const int visc = c->mu > 0.0 ? 1 : 0;
   if (c->mp_mode == GBR_MP_EVERYWHERE)
-    return kVariants[v].mpe[c->recon == GBR_RECON_CONS ? 1 : 0][visc];
+    return tile_variants()[v].mpe[c->recon == GBR_RECON_CONS ? 1 : 0][visc];
   if (c->riemann == GBR_RIEMANN_HLLC_SS)
-    return kVariants[v].ss[c->recon == GBR_RECON_CONS ? 1 : 0][visc];
-  if (c->order == 4) return kVariants[v].g4[c->recon == GBR_RECON_CONS ? 1 : 0][visc];
-  if (c->recon == GBR_RECON_CONS) return kVariants[v].cons[visc];
+    return tile_variants()[v].ss[c->recon == GBR_RECON_CONS ? 1 : 0][visc];
+  if (c->order == 4) return tile_variants()[v].g4[c->recon == GBR_RECON_CONS ? 1 : 0][visc];
+  if (c->recon == GBR_RECON_CONS) return tile_variants()[v].cons[visc];
   const int prec = c->precision == GBR_PREC_FP32_BULK ? 1 : 0;
   const int det = c->detector == GBR_DET_MLP ? 1 : 0;
-  return kVariants[v].fn[prec][visc][det];
+  return tile_variants()[v].fn[prec][visc][det];
 }
 static int active_variant(const gbr_ctx* c) { return variant_fn(c, c->tiling) ? c->tiling : 0; }
 
@@ -538,14 +400,14 @@ static int launch_stage(gbr_ctx* c, int mode, const double* dt, const double* Qn
   }
   if (det) P.chimap = c->d_chimap;
   const int vi = active_variant(c);
-  const TileVariant* v = &kVariants[vi];
+  const TileVariant* v = &tile_variants()[vi];
   P.tiles_x = (c->nx + v->tx - 1) / v->tx;
   P.ntiles = P.tiles_x * ((c->ny + v->ty - 1) / v->ty);
   if (tev && hipEventRecord(tev[1], s) != hipSuccess) return GBR_EDEVICE;
-  variant_fn(c, vi)(P, s);
+  const int waves = variant_fn(c, vi)(P, s);
   if (tev && hipEventRecord(tev[2], s) != hipSuccess) return GBR_EDEVICE;
   if (mode == MODE_STAGE3) {
-    c->stage3_slots = P.ntiles * kStageWaves;
+    c->stage3_slots = P.ntiles * waves;
     c->rp_valid = P.rp != nullptr;
     c->rp_src = out;
     c->rp_armed = 0;
@@ -589,8 +451,8 @@ int gbr_set_tiling(gbr_ctx* c, int variant) {
 
 int gbr_get_tiling(gbr_ctx* c, int* variant, int* tile_x, int* tile_y) {
   if (!c) return GBR_EINVAL;
-  const TileVariant* v = &kVariants[active_variant(c)];
-  if (variant) *variant = (int)(v - kVariants);
+  const TileVariant* v = &tile_variants()[active_variant(c)];
+  if (variant) *variant = (int)(v - tile_variants());
   if (tile_x) *tile_x = v->tx;
   if (tile_y) *tile_y = v->ty;
   return GBR_OK;
@@ -951,7 +813,7 @@ static void batch_drop_graphs(gbr_batch* b) {
 
 // Tile table and launch size for the current tile shape.
 static int batch_layout(gbr_batch* b) {
-  const BatchVariant& v = kBatchVariants[b->tiling];
+  const BatchVariant& v = batch_variants()[b->tiling];
   std::vector<int> ts(b->nprob + 1);
   long long t = 0;
   for (int p = 0; p < b->nprob; ++p) {
@@ -1022,7 +884,7 @@ static void batch_launch_stage(gbr_batch* b, int x, int st, hipStream_t s) {
   B.tile_start = b->d_tile_start;
   B.nprob = b->nprob;
   B.total = b->total;
-  kBatchVariants[b->tiling].fn[b->precision == GBR_PREC_FP32_BULK ? 1 : 0](B, b->grid, s);
+  batch_variants()[b->tiling].fn[b->precision == GBR_PREC_FP32_BULK ? 1 : 0](B, b->grid, s);
 }
 
 // One SSP-RK3 step from array set x: stages into y, z, y (y = x+1, z = x+2
@@ -1149,8 +1011,8 @@ int gbr_batch_info(gbr_batch* b, int* tiling, int* tile_x, int* tile_y, int* tot
                    int* workgroups) {
   if (!b) return GBR_EINVAL;
   if (tiling) *tiling = b->tiling;
-  if (tile_x) *tile_x = kBatchVariants[b->tiling].tx;
-  if (tile_y) *tile_y = kBatchVariants[b->tiling].ty;
+  if (tile_x) *tile_x = batch_variants()[b->tiling].tx;
+  if (tile_y) *tile_y = batch_variants()[b->tiling].ty;
   if (total_tiles) *total_tiles = b->total;
   if (workgroups) *workgroups = b->grid;
   return GBR_OK;

@@ -326,9 +326,11 @@ __device__ __forceinline__ void cons_to_prim(const double Q[4], double gamma, do
 // columns of R = L^{-1}: (1, u-c, v, H-uc), (1, u, v, (u^2+v^2)/2), (0, 0, 1, v),
 //   (1, u+c, v, H+uc).  Every row reads all four fields, so the rows are
 // limited one at a time in a rolled loop and projected back column by column.
-template <int ORD = 7, class FQ, class FG>
-__device__ __forceinline__ void meg7_char_states_cons(FQ Qf, FG Gf, double gamma,
-                                                      double QLo[4], double QRo[4]) {
+// CG(l, cv, cg) writes the combination sum_f l[f] field f and its gradient at
+// the six offsets.
+template <int ORD = 7, class FQ, class FC>
+__device__ __forceinline__ void meg7_char_states_cons_comb(FQ Qf, FC CG, double gamma,
+                                                           double QLo[4], double QRo[4]) {
   const double q0 = 0.5 * (Qf(2, 0) + Qf(3, 0)), q1 = 0.5 * (Qf(2, 1) + Qf(3, 1));
   const double q2 = 0.5 * (Qf(2, 2) + Qf(3, 2)), q3 = 0.5 * (Qf(2, 3) + Qf(3, 3));
   const double iq0 = rcp_nr(q0);
@@ -359,11 +361,8 @@ __device__ __forceinline__ void meg7_char_states_cons(FQ Qf, FG Gf, double gamma
       l3 = 0.5 * b1;
     }
     double cv[6], cg[6];
-#pragma unroll
-    for (int q = 0; q < 6; ++q) {
-      cv[q] = l0 * Qf(q, 0) + l1 * Qf(q, 1) + l2 * Qf(q, 2) + l3 * Qf(q, 3);
-      cg[q] = l0 * Gf(q, 0) + l1 * Gf(q, 1) + l2 * Gf(q, 2) + l3 * Gf(q, 3);
-    }
+    const double lm[4] = {l0, l1, l2, l3};
+    CG(lm, cv, cg);
     double cl, cr;
     meg7_pair<ORD>(cv, cg, cl, cr);
     double r0, r1, r2, r3;
@@ -377,6 +376,48 @@ __device__ __forceinline__ void meg7_char_states_cons(FQ Qf, FG Gf, double gamma
     QLo[0] += r0 * cl; QLo[1] += r1 * cl; QLo[2] += r2 * cl; QLo[3] += r3 * cl;
     QRo[0] += r0 * cr; QRo[1] += r1 * cr; QRo[2] += r2 * cr; QRo[3] += r3 * cr;
   }
+}
+
+// The same with staged gradients.
+template <int ORD = 7, class FQ, class FG>
+__device__ __forceinline__ void meg7_char_states_cons(FQ Qf, FG Gf, double gamma,
+                                                      double QLo[4], double QRo[4]) {
+  meg7_char_states_cons_comb<ORD>(
+      Qf,
+      [&](const double l[4], double cv[6], double cg[6]) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+          cv[q] = l[0] * Qf(q, 0) + l[1] * Qf(q, 1) + l[2] * Qf(q, 2) + l[3] * Qf(q, 3);
+          cg[q] = l[0] * Gf(q, 0) + l[1] * Gf(q, 1) + l[2] * Gf(q, 2) + l[3] * Gf(q, 3);
+        }
+      },
+      gamma, QLo, QRo);
+}
+
+// The same from the cells alone: Vc(k, f) is field f at offset k - 5 from cell
+// j, k = 0..11; the gradients are those of eq. (eqn:six) on the jumps of the
+// combination itself.
+template <int ORD = 7, class FV>
+__device__ __forceinline__ void meg7_char_states_cons_cells(FV Vc, double gamma, double QLo[4],
+                                                            double QRo[4]) {
+  meg7_char_states_cons_comb<ORD>(
+      [&](int q, int f) { return Vc(q + 3, f); },
+      [&](const double l[4], double cv[6], double cg[6]) {
+        double cc[12], ce[11];
+#pragma unroll
+        for (int k = 0; k < 12; ++k)
+          cc[k] = l[0] * Vc(k, 0) + l[1] * Vc(k, 1) + l[2] * Vc(k, 2) + l[3] * Vc(k, 3);
+#pragma unroll
+        for (int a = 0; a < 11; ++a) ce[a] = cc[a + 1] - cc[a];
+        constexpr double z = 1.0 / 60.0;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+          cv[q] = cc[q + 3];
+          cg[q] = z * (37.0 * (ce[q + 2] + ce[q + 3]) - 8.0 * (ce[q + 1] + ce[q + 4]) +
+                       (ce[q] + ce[q + 5]));
+        }
+      },
+      gamma, QLo, QRo);
 }
 
 // Normal convective flux of the state W (Sec. 1 flux vectors, rotated).

@@ -1,18 +1,17 @@
-// Fused MEG7 residual + SSP-RK3 stage kernel for gfx950 (FP64 path).
+// Fused MEG7 residual + SSP-RK3 stage for gfx950 (FP64): what every 2D stage
+// kernel shares -- parameters, tile load with the boundary rules, stage store
+// with the time-step extrema -- and the kernel of the MP test at every
+// interface (the other variants: stage_line.hpp).
 //
-// One workgroup owns a TX x TY tile of cells.  It stages the tile plus a
-// 6-cell halo of primitive variables in LDS once (periodic wrap or
-// transmissive clamp in the index math), then sweeps x and y:
-//   pass 1 (per cell):      edge jumps of the reconstructed fields (and of
-//                           T, viscous) from which the sixth-order gradients
-//                           of eq. (eqn:six) are formed where read; staged
-//                           gradients instead for MEG7-cons and the MP test
-//                           everywhere; density detector (Sec. 2.4),
-//                           cell-centre fluxes;
+// In that kernel one workgroup owns a TX x TY tile of cells.  It stages the
+// tile plus a 6-cell halo in LDS once, then sweeps x and y:
+//   pass 1 (per cell):      staged sixth-order gradients of eq. (eqn:six),
+//                           density detector (Sec. 2.4), cell-centre fluxes;
 //   pass 2 (per interface): sigma from the 6-cell buffer; smooth interfaces
-//                           take GRB states + flux reconstruction + HLLC +
-//                           viscous flux at once; flagged ones are compacted
-//                           with a wavefront ballot into an LDS queue;
+//                           take the characteristic MEG7 states + flux
+//                           reconstruction + HLLC + viscous flux at once;
+//                           flagged ones are compacted with a wavefront
+//                           ballot into an LDS queue;
 //   pass 3 (queue):         characteristic MP (MEG7) states, F(Q), HLLC;
 //   pass 4 (per cell):      flux differences accumulated in registers.
 // The x sweep runs in sub-blocks of SX rows, the y sweep in sub-blocks of SY
@@ -75,53 +74,38 @@ __device__ __forceinline__ int bc_index(int k, int n, int bc) {
   return k < 0 ? 0 : (k >= n ? n - 1 : k);
 }
 
-template <int TX_, int TY_, int SX_, int SY_, int NT_, bool VISC_, int MINW_ = 2>
+template <int TX_, int TY_, int SX_, int SY_, int NT_, bool VISC_>
 struct TileCfg {
   static constexpr int TX = TX_, TY = TY_, SX = SX_, SY = SY_, NT = NT_;
-  static constexpr int MINW = MINW_;  // waves per SIMD the register budget must allow
   static constexpr bool VISC = VISC_;
   static constexpr int H = 6;
   static constexpr int RX = TX + 2 * H, RY = TY + 2 * H, RS = RX * RY;
+  // cells staged: the whole tile and halo, row by row
+  static constexpr int NLOAD = RS;
+  __device__ static __forceinline__ void cell(int c, int& lx, int& ly) {
+    ly = c / RX - H;
+    lx = c - (ly + H) * RX - H;
+  }
   static constexpr int cmax(int a, int b) { return a > b ? a : b; }
-  // Per-line buffers of a sweep: a first buffer of NE fields and the cell
-  // fluxes (then the interface fluxes).  The first buffer holds either the
-  // normal gradients of the four reconstructed fields (MEG7-cons, MP test
-  // everywhere) or the edge jumps of those fields, from which every gradient
-  // is formed where it is read (the edge form: the other variants); the
-  // viscous edge form adds the edge jumps of T as a fifth field, and its tile
-  // then holds no T.  The tangential derivatives of u_n, u_t are formed from
-  // the tile where an interface needs them.
-  template <int N, int NL, int NE = 4, bool EDGE = true>
+  // Per-line buffers of a sweep: the normal gradients of the four
+  // reconstructed fields and the cell fluxes (then the interface fluxes).
+  // The tangential derivatives of u_n, u_t are formed from the tile where an
+  // interface needs them.
+  template <int N, int NL>
   struct Phase {
     static constexpr int WD = N + 6, WF = N + 10, WFL = N + 1;
-    static constexpr int WE = N + 10;   // edges j+1/2, j in [-5, N+5)
-    static constexpr int D = NE * NL * (EDGE ? WE : WD);
-    static constexpr int F = 4 * NL * (WF > WFL ? WF : WFL);
-    static constexpr int TOT = D + F;
-  };
-  template <bool EDGE>
-  struct Layout {
-    static constexpr bool TFIELD = VISC && !EDGE;   // the tile holds T
-    static constexpr int NFU = TFIELD ? 5 : 4;      // tile fields
-    static constexpr int NE = VISC && EDGE ? 5 : 4;
-    static constexpr int PH = cmax(Phase<TX, SX, NE, EDGE>::TOT, Phase<TY, SY, NE, EDGE>::TOT);
+    static constexpr int D = 4 * NL * WD;
+    static constexpr int TOT = D + 4 * NL * WF;
   };
   using PX = Phase<TX, SX>;
   using PY = Phase<TY, SY>;
-  // the larger of the two layouts (the LDS bound checked at the launch sites)
-  static constexpr int NF = cmax(Layout<false>::NFU, Layout<true>::NFU);
-  static constexpr int PH = cmax(Layout<false>::PH, Layout<true>::PH);
+  static constexpr int NF = VISC ? 5 : 4;   // tile fields
+  static constexpr int PH = cmax(PX::TOT, PY::TOT);
   static constexpr int CHI = cmax(SX * PX::WD, SY * PY::WD);
   static constexpr int QMAX = cmax(SX * PX::WFL, SY * PY::WFL);
   static constexpr int CPT = (TX * TY + NT - 1) / NT;
   static constexpr int LDS_BYTES = 8 * (NF * RS + PH) + CHI + 2 * QMAX + 16;
 };
-
-// The edge form (per-line edge jumps instead of staged gradients) serves
-// every variant but MEG7-cons and the MP test at every interface, which read
-// many gradients per interface.
-template <bool CONS, bool MPE>
-constexpr bool edge_form() { return !CONS && !MPE; }
 
 // Cell slot k of thread tid: tile cell (lx, ly); false for an idle slot.
 // Row-major in general.  For 15 x 15 tiles on 256 threads each half-wave
@@ -152,7 +136,6 @@ struct Lds {
   unsigned char* chi;
   unsigned short* queue;
   int* qcount;
-  const unsigned char* chif;   // per-cell learned-detector flags (bit 0 x, bit 1 y)
 };
 
 // Index of tile cell (lx, ly), lx in [-3, TX+3), ly in [-3, TY+3), in the
@@ -198,17 +181,15 @@ __device__ __forceinline__ void put_chimap(const ChiMap<C>& m, unsigned char* ch
   }
 }
 
-template <class C, int DIR, bool DETMLP, bool CONS, int ORD, bool LM, bool MPE>
+template <class C, int DIR, bool CONS>
 __device__ __forceinline__ void sweep(const StageParams& P, const Lds& L, int l0, int tx0,
                                       int ty0, double (&res)[C::CPT][4]) {
   constexpr bool X = (DIR == 0);
   constexpr int N = X ? C::TX : C::TY;
   constexpr int NL = X ? C::SX : C::SY;
   constexpr int NLINES = X ? C::TY : C::TX;
-  constexpr bool EDGE = edge_form<CONS, MPE>();
-  constexpr bool ET = C::VISC && EDGE;   // T edges in the first buffer, no T in the tile
-  using PH = typename C::template Phase<N, NL, C::template Layout<EDGE>::NE, EDGE>;
-  constexpr int WD = PH::WD, WF = PH::WF, WFL = PH::WFL, WE = PH::WE;
+  using PH = typename C::template Phase<N, NL>;
+  constexpr int WD = PH::WD, WF = PH::WF, WFL = PH::WFL;
   constexpr int RS = C::RS, RX = C::RX, H = C::H, NT = C::NT;
   constexpr int SN = X ? 1 : RX;  // normal stride in the LDS tile
   constexpr int ST = X ? RX : 1;  // tangential stride
@@ -220,10 +201,9 @@ __device__ __forceinline__ void sweep(const StageParams& P, const Lds& L, int l0
   const double inv_dn = X ? P.inv_dx : P.inv_dy;
   const double inv_dt = X ? P.inv_dy : P.inv_dx;
 
-  double* sD = L.ph;                       // [4][NL x WD]   normal gradients (rotated order), or
-  double* sE = L.ph;                       // [4|5][NL x WE] edge jumps (rotated order, then T) at j + 5
+  double* sD = L.ph;                       // [4][NL x WD]   normal gradients (rotated order)
   double* sF = sD + PH::D;                 // [4][NL x WF]   cell fluxes; later [4][NL x WFL] interface fluxes
-  constexpr int FSTR = (WF > WFL ? WF : WFL) * NL;
+  constexpr int FSTR = WF * NL;
   // interface values: odd row stride, so pass 4 (lanes across lines in the
   // y sweep) reads distinct banks
   constexpr int WFS = WFL | 1;
@@ -253,52 +233,19 @@ __device__ __forceinline__ void sweep(const StageParams& P, const Lds& L, int l0
     const double* u = L.U + f * RS + r;
     return grad6(u[-3 * d], u[-2 * d], u[-d], u[d], u[2 * d], u[3 * d]);
   };
-  // Edge form: edge jump j+1/2 of rotated field m (m < 4) on line `line`
-  // (pass 1 stores j in [-5, N+5); the edge j = -6, which only gradients at
-  // a line's first interface reach, is formed from the tile), and the normal
-  // gradient of eq. (eqn:six) at cell k on the edges: the stencil
-  // (45, -9, 1)/60 on value differences becomes (37, -8, 1)/60 on the pairs
-  // of edges around k.
-  auto edge = [&](int m, int line, int j) -> double {
-    if (j < -5) {
-      const double* u = L.U + rot[m] * RS + ridx(line, -6);
-      return u[SN] - u[0];
-    }
-    return sE[m * NL * WE + bidx(line, j + 5, WE)];
-  };
-  auto g6e = [](double e0, double e1, double e2, double e3, double e4, double e5) {
-    constexpr double z = 1.0 / 60.0;
-    return z * (37.0 * (e2 + e3) - 8.0 * (e1 + e4) + (e0 + e5));
-  };
-  auto gradE = [&](int m, int line, int k) -> double {
-    return g6e(edge(m, line, k - 3), edge(m, line, k - 2), edge(m, line, k - 1),
-               edge(m, line, k), edge(m, line, k + 1), edge(m, line, k + 2));
-  };
   // normal gradient of rotated field m at cell k of line `line`
   auto grad_at = [&](int m, int line, int k) -> double {
-    if constexpr (EDGE) return gradE(m, line, k);
-    else return sD[m * NL * WD + bidx(line, k + 3, WD)];
+    return sD[m * NL * WD + bidx(line, k + 3, WD)];
   };
   // Normal differences the viscous flux of interface (line, pos + 1/2)
   // takes, r its left cell: gv = {g(u_n), g(u_n)', g(u_t), g(u_t)', g(T),
   // g(T)', T' - T} (g at the left cell, ' at the right one; velocity entries
-  // for the primitive forms only, and only with vel)
-  auto visc_normal = [&](int line, int pos, int r, double* gv, bool vel) {
-    if constexpr (ET) {
-      // T edges pos-3 .. pos+3: stored for every interface pos in [-1, N)
-      const double* e = sE + 4 * NL * WE;
-      double t[7];
-#pragma unroll
-      for (int a = 0; a < 7; ++a) t[a] = e[bidx(line, pos + a + 2, WE)];
-      gv[4] = g6e(t[0], t[1], t[2], t[3], t[4], t[5]);
-      gv[5] = g6e(t[1], t[2], t[3], t[4], t[5], t[6]);
-      gv[6] = t[3];
-    } else {
-      gv[4] = g6(4, r, SN);
-      gv[5] = g6(4, r + SN, SN);
-      gv[6] = L.U[4 * RS + r + SN] - L.U[4 * RS + r];
-    }
-    if (!CONS && vel) {
+  // for the primitive form only)
+  auto visc_normal = [&](int line, int pos, int r, double* gv) {
+    gv[4] = g6(4, r, SN);
+    gv[5] = g6(4, r + SN, SN);
+    gv[6] = L.U[4 * RS + r + SN] - L.U[4 * RS + r];
+    if (!CONS) {
       gv[0] = grad_at(1, line, pos);
       gv[1] = grad_at(1, line, pos + 1);
       gv[2] = grad_at(2, line, pos);
@@ -366,38 +313,17 @@ __device__ __forceinline__ void sweep(const StageParams& P, const Lds& L, int l0
 #pragma unroll
       for (int m = 0; m < 4; ++m) sF[m * FSTR + bidx(line, p, WF)] = f[m];
     }
-    if (EDGE) {
-      // edge jump pos + 1/2, pos in [-5, N+5)
+    if (pos >= -3 && pos < N + 3) {
+      const int pd = pos + 3;
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
         const double* u = U + rot[m] * RS + r;
-        sE[m * NL * WE + bidx(line, pos + 5, WE)] = u[SN] - u[0];
+        sD[m * NL * WD + bidx(line, pd, WD)] =
+            grad6(u[-3 * SN], u[-2 * SN], u[-SN], u[SN], u[2 * SN], u[3 * SN]);
       }
-      if (ET) {
-        // T = gamma p / rho on both sides (the tile holds no T)
-        const double T0 = P.gamma * U[3 * RS + r] * rcp_nr(U[r]);
-        const double T1 = P.gamma * U[3 * RS + r + SN] * rcp_nr(U[r + SN]);
-        sE[4 * NL * WE + bidx(line, pos + 5, WE)] = T1 - T0;
-      }
-    }
-    if (pos >= -3 && pos < N + 3) {
-      const int pd = pos + 3;
-      if (!EDGE) {
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          const double* u = U + rot[m] * RS + r;
-          sD[m * NL * WD + bidx(line, pd, WD)] =
-              grad6(u[-3 * SN], u[-2 * SN], u[-SN], u[SN], u[2 * SN], u[3 * SN]);
-        }
-      }
-      if (DETMLP) {
-        L.chi[bidx(line, pd, WD)] =
-            (L.chif[mlp_chi_index<C>(X ? pos : l0 + line, X ? l0 + line : pos)] >> DIR) & 1;
-      } else {
-        const double* rho = U + r;
-        L.chi[bidx(line, pd, WD)] =
-            detector_flag(rho[-2 * SN], rho[-SN], rho[0], rho[SN], rho[2 * SN]) ? 1 : 0;
-      }
+      const double* rho = U + r;
+      L.chi[bidx(line, pd, WD)] =
+          detector_flag(rho[-2 * SN], rho[-SN], rho[0], rho[SN], rho[2 * SN]) ? 1 : 0;
     }
   }
   if (tid == 0) *L.qcount = 0;
@@ -432,73 +358,25 @@ __device__ __forceinline__ void sweep(const StageParams& P, const Lds& L, int l0
         flagged = !sigma;
         if (sigma) {
           const int r = ridx(line, pos);
-          double WL[4], WR[4], Fm[4], gv[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+          double WL[4], WR[4], Fm[4];
 #pragma unroll
           for (int m = 0; m < 4; ++m) {
-            const double* u = L.U + rot[m] * RS + r;
-            if constexpr (EDGE) {
-              // eq. (eqn:grb) (ORD 7) or its fourth-order subset with the
-              // gradients of eq. (eqn:six) substituted, minus Phi_j (resp.
-              // Phi_{j+1}): stencils on the edge jumps E[a] at (pos+a-4)+1/2
-              double E[9];
-#pragma unroll
-              for (int a = 0; a < 9; ++a) E[a] = sE[m * NL * WE + bidx(line, pos + a + 1, WE)];
-              double cL, cR;
-              if (ORD == 4) {
-                constexpr double s4 = 1.0 / 1440.0;
-                cL = s4 * ((E[0] - E[7]) + 4.0 * E[1] - 60.0 * E[2] + 249.0 * E[3] + 639.0 * E[4] -
-                           132.0 * E[5] + 20.0 * E[6]);
-                cR = s4 * ((E[1] - E[8]) - 20.0 * E[2] + 132.0 * E[3] - 639.0 * E[4] -
-                           249.0 * E[5] + 60.0 * E[6] - 4.0 * E[7]);
-              } else {
-                constexpr double s7 = 1.0 / 840.0;
-                cL = s7 * ((E[0] - E[1] - E[7]) - 23.0 * E[2] + 123.0 * E[3] + 395.0 * E[4] -
-                           89.0 * E[5] + 15.0 * E[6]);
-                cR = s7 * ((E[1] - E[8] + E[7]) - 15.0 * E[2] + 89.0 * E[3] - 395.0 * E[4] -
-                           123.0 * E[5] + 23.0 * E[6]);
-              }
-              WL[m] = u[0] + cL;
-              WR[m] = u[SN] + cR;
-              if (C::VISC && (m == 1 || m == 2)) {
-                // velocity gradients at cells pos, pos+1 from the same edges
-                gv[2 * m - 2] = g6e(E[1], E[2], E[3], E[4], E[5], E[6]);
-                gv[2 * m - 1] = g6e(E[2], E[3], E[4], E[5], E[6], E[7]);
-              }
-            } else {
-              double v[6], g[6];
-#pragma unroll
-              for (int q = 0; q < 6; ++q) v[q] = u[(q - 2) * SN];
-#pragma unroll
-              for (int q = 1; q < 5; ++q) g[q] = sD[m * NL * WD + bidx(line, pos + q + 1, WD)];
-              g[0] = g[5] = 0.0;
-              WL[m] = grb_l<ORD>(v, g);
-              WR[m] = grb_r<ORD>(v, g);
-            }
             // (F(f_L) + F(f_R))/2 on the cell fluxes f_{j-4..j+5}
             double f[10];
 #pragma unroll
             for (int q = 0; q < 10; ++q) f[q] = sF[m * FSTR + bidx(line, pos + q + 1, WF)];
-            Fm[m] = flux_mean<ORD>(f);
+            Fm[m] = flux_mean<7>(f);
           }
-          if (MPE) {
-            // MP test at every interface (mp_mode everywhere): the states are
-            // the characteristic MEG7 ones; the fluxes stay reconstructed
-            auto Vf = [&](int q, int f) { return L.U[rot[f] * RS + r + (q - 2) * SN]; };
-            auto Gf = [&](int q, int f) { return sD[f * NL * WD + bidx(line, pos + q + 1, WD)]; };
-            if (CONS) {
-              double QL[4], QR[4];
-              meg7_char_states_cons<ORD>(Vf, Gf, P.gamma, QL, QR);
-              cons_to_prim(QL, P.gamma, WL);
-              cons_to_prim(QR, P.gamma, WR);
-            } else {
-              meg7_char_states<ORD>(Vf, Gf, P.gamma, WL, WR);
-            }
-          } else if (CONS) {
-            // the GRB states above are conservative: to primitives
-            const double QL[4] = {WL[0], WL[1], WL[2], WL[3]};
-            const double QR[4] = {WR[0], WR[1], WR[2], WR[3]};
+          // the characteristic MEG7 states; the fluxes stay reconstructed
+          auto Vf = [&](int q, int f) { return L.U[rot[f] * RS + r + (q - 2) * SN]; };
+          auto Gf = [&](int q, int f) { return grad_at(f, line, pos + q - 2); };
+          if (CONS) {
+            double QL[4], QR[4];
+            meg7_char_states_cons<7>(Vf, Gf, P.gamma, QL, QR);
             cons_to_prim(QL, P.gamma, WL);
             cons_to_prim(QR, P.gamma, WR);
+          } else {
+            meg7_char_states<7>(Vf, Gf, P.gamma, WL, WR);
           }
           if (!(WL[0] > 0.0 && WL[3] > 0.0 && WR[0] > 0.0 && WR[3] > 0.0)) {
             // unphysical reconstruction: first-order states and fluxes
@@ -518,10 +396,10 @@ __device__ __forceinline__ void sweep(const StageParams& P, const Lds& L, int l0
 #pragma unroll
             for (int m = 0; m < 4; ++m) Fm[m] = 0.5 * (f0[m] + f1[m]);
           }
-          hllc<LM>(WL, WR, Fm, P.gamma, P.g1inv, fsm[k]);
+          hllc(WL, WR, Fm, P.gamma, P.g1inv, fsm[k]);
           if (C::VISC) {
-            // edge form: the velocity entries came with the GRB states above
-            visc_normal(line, pos, r, gv, !EDGE);
+            double gv[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+            visc_normal(line, pos, r, gv);
             visc_at(line, pos, r, gv, fsm[k]);
           }
           has[k] = true;
@@ -565,17 +443,13 @@ __device__ __forceinline__ void sweep(const StageParams& P, const Lds& L, int l0
     double WL[4], WR[4];
     auto Vf = [&](int q, int f) { return U[rot[f] * RS + r + (q - 2) * SN]; };
     auto Gf = [&](int q, int f) { return grad_at(f, line, pos + q - 2); };
-    // edge form: the jumps across edges (pos-5)+1/2 .. (pos+5)+1/2
-    auto Ef = [&](int a, int f) { return edge(f, line, pos - 5 + a); };
     if (CONS) {
       double QL[4], QR[4];
-      meg7_char_states_cons<ORD>(Vf, Gf, P.gamma, QL, QR);
+      meg7_char_states_cons<7>(Vf, Gf, P.gamma, QL, QR);
       cons_to_prim(QL, P.gamma, WL);
       cons_to_prim(QR, P.gamma, WR);
-    } else if constexpr (EDGE) {
-      meg7_char_states_edges<ORD>(Vf, Ef, P.gamma, WL, WR);
     } else {
-      meg7_char_states<ORD>(Vf, Gf, P.gamma, WL, WR);
+      meg7_char_states<7>(Vf, Gf, P.gamma, WL, WR);
     }
     if (!(WL[0] > 0.0 && WL[3] > 0.0 && WR[0] > 0.0 && WR[3] > 0.0)) {
       if (CONS) {
@@ -594,10 +468,10 @@ __device__ __forceinline__ void sweep(const StageParams& P, const Lds& L, int l0
     conv_flux(WR, P.g1inv, FR);
 #pragma unroll
     for (int m = 0; m < 4; ++m) Fm[m] = 0.5 * (FL[m] + FR[m]);
-    hllc<LM>(WL, WR, Fm, P.gamma, P.g1inv, F);
+    hllc(WL, WR, Fm, P.gamma, P.g1inv, F);
     if (C::VISC) {
       double gv[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-      visc_normal(line, pos, r, gv, true);
+      visc_normal(line, pos, r, gv);
       visc_at(line, pos, r, gv, F);
     }
 #pragma unroll
@@ -688,13 +562,12 @@ __device__ __forceinline__ unsigned ghost_op(int kx, int ky, int sx, int gx, int
   return op;
 }
 
-// TFIELD: whether the tile holds T (the FP64 viscous kernels of MEG7-cons
-// and of the MP test everywhere; the edge-form and FP32 ones form T where
-// they need it).
+// TFIELD: whether the tile holds T (the viscous MP-everywhere kernels; the
+// line-streamed ones form T where they need it).
 template <class C, bool CONS = false, bool TFIELD = C::VISC>
 __device__ __forceinline__ void stage_load(const StageParams& P, double* sU, int tx0, int ty0) {
   constexpr int RS = C::RS, RX = C::RX, H = C::H, NT = C::NT, TX = C::TX, TY = C::TY;
-  constexpr int LR = (RS + NT - 1) / NT;
+  constexpr int NLOAD = C::NLOAD, LR = (NLOAD + NT - 1) / NT;
   const int tid = threadIdx.x;
   const size_t n = (size_t)P.nx * P.ny;
   bool bad = false;
@@ -743,8 +616,9 @@ __device__ __forceinline__ void stage_load(const StageParams& P, double* sU, int
 #pragma unroll
     for (int k = 0; k < LR; ++k) {
       const int c = tid + k * NT;
-      if (c < RS) {
-        const int ly = c / RX - H, lx = c - (ly + H) * RX - H;
+      if (c < NLOAD) {
+        int lx, ly;
+        C::cell(c, lx, ly);
         const int gi = inner ? ty0 + ly : bc_index(ty0 + ly, P.ny, P.bcy);
         const int gj = inner ? tx0 + lx : bc_index(tx0 + lx, P.nx, P.bcx);
         const int o = gi * P.nx + gj;
@@ -757,8 +631,9 @@ __device__ __forceinline__ void stage_load(const StageParams& P, double* sU, int
 #pragma unroll
     for (int k = 0; k < LR; ++k) {
       const int c = tid + k * NT;
-      if (c < RS) {
-        const int ly = c / RX - H, lx = c - (ly + H) * RX - H;
+      if (c < NLOAD) {
+        int lx, ly;
+        C::cell(c, lx, ly);
         put(lx, ly, q[k][0], q[k][1], q[k][2], q[k][3], 0u);
       }
     }
@@ -770,8 +645,9 @@ __device__ __forceinline__ void stage_load(const StageParams& P, double* sU, int
       tb = *P.tnow + (P.tc != 0.0 ? P.tc * *P.dt : 0.0);
     }
 #pragma unroll 1
-    for (int c = tid; c < RS; c += NT) {
-      const int ly = c / RX - H, lx = c % RX - H;
+    for (int c = tid; c < NLOAD; c += NT) {
+      int lx, ly;
+      C::cell(c, lx, ly);
       const int i = ty0 + ly, j = tx0 + lx;
       double xc, yc;
       {
@@ -962,49 +838,27 @@ __device__ __forceinline__ void stage_store(const StageParams& P, const double (
   }
 }
 
-// One tile of the stage: load, both sweeps, store.  The LDS arrays are
-// passed in so that a kernel can run several tile shapes from one set of
-// arrays sized for the largest (the batched kernel).
-template <class C, bool DETMLP, bool CONS = false, int ORD = 7, bool LM = false,
-          bool MPE = false>
-__device__ __forceinline__ void stage_tile(const StageParams& P, int tx0, int ty0, double* sU,
-                                           double* sPh, unsigned char* sChi,
-                                           unsigned short* sQueue, int* sQCount,
-                                           unsigned char* sChiF) {
-  ChiMap<C> cm;
-  if (DETMLP) fetch_chimap<C>(P, cm, tx0, ty0);
-  stage_load<C, CONS, C::template Layout<edge_form<CONS, MPE>()>::TFIELD>(P, sU, tx0, ty0);
-  if (DETMLP) put_chimap<C>(cm, sChiF);
+// The stage with the MP test at every interface.
+template <class C, bool CONS>
+__global__ __launch_bounds__(C::NT, 2) void meg7_stage_kernel(StageParams P) {
+  __shared__ double sU[C::NF * C::RS];
+  __shared__ double sPh[C::PH];
+  __shared__ unsigned char sChi[C::CHI];
+  __shared__ unsigned short sQueue[C::QMAX];
+  __shared__ int sQCount;
+  int tx0, ty0;
+  if (!tile_origin(P, C::TX, C::TY, tx0, ty0)) return;
+  stage_load<C, CONS, C::VISC>(P, sU, tx0, ty0);
   __syncthreads();
-  const Lds L{sU, sPh, sChi, sQueue, sQCount, sChiF};
+  const Lds L{sU, sPh, sChi, sQueue, &sQCount};
   double res[C::CPT][4];
 #pragma unroll
   for (int k = 0; k < C::CPT; ++k)
 #pragma unroll
     for (int m = 0; m < 4; ++m) res[k][m] = 0.0;
-  for (int l0 = 0; l0 < C::TY; l0 += C::SX)
-    sweep<C, 0, DETMLP, CONS, ORD, LM, MPE>(P, L, l0, tx0, ty0, res);
-  for (int l0 = 0; l0 < C::TX; l0 += C::SY)
-    sweep<C, 1, DETMLP, CONS, ORD, LM, MPE>(P, L, l0, tx0, ty0, res);
+  for (int l0 = 0; l0 < C::TY; l0 += C::SX) sweep<C, 0, CONS>(P, L, l0, tx0, ty0, res);
+  for (int l0 = 0; l0 < C::TX; l0 += C::SY) sweep<C, 1, CONS>(P, L, l0, tx0, ty0, res);
   stage_store<C>(P, res, tx0, ty0);
-}
-
-// The MP test at every interface needs more registers than any budget of
-// three waves per SIMD leaves without spilling: those variants get two.
-template <class C, bool DETMLP, bool CONS = false, int ORD = 7, bool LM = false, bool MPE = false>
-__global__ __launch_bounds__(C::NT, (MPE && C::MINW > 2) ? 2 : C::MINW) void meg7_stage_kernel(
-    StageParams P) {
-  using LY = typename C::template Layout<edge_form<CONS, MPE>()>;
-  __shared__ double sU[LY::NFU * C::RS];
-  __shared__ double sPh[LY::PH];
-  __shared__ unsigned char sChi[C::CHI];
-  __shared__ unsigned short sQueue[C::QMAX];
-  __shared__ unsigned char sChiF[DETMLP ? (C::TX + 6) * (C::TY + 6) : 1];
-  __shared__ int sQCount;
-  int tx0, ty0;
-  if (!tile_origin(P, C::TX, C::TY, tx0, ty0)) return;
-  stage_tile<C, DETMLP, CONS, ORD, LM, MPE>(P, tx0, ty0, sU, sPh, sChi, sQueue, &sQCount,
-                                            sChiF);
 }
 
 }  // namespace gbr
