@@ -44,16 +44,11 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 # write Q^(k+1) (32 B), and Q^n (32 B) in stages 2 and 3; 256/3 B on average.
 BYTES_PER_CELL_STAGE = {1: 64.0, 2: 96.0, 3: 96.0}
 
-# 3D (40 B per cell state): the x sweep reads Q^(k) and writes the residual
-# accumulator (80 B), the y sweep reads Q^(k) and the accumulator and writes it
-# (120 B), the z sweep reads Q^(k) and the accumulator, writes the result and
-# reads Q^n (stage 1) or Q^n and Q^(k) (stages 2, 3) for the update:
-# 120 + (40 + 80 + 80)/3 B.  Per cell-stage on average:
-BYTES_PER_CELL_STAGE_3D = 80.0 + 120.0 + 120.0 + 200.0 / 3.0
-# With the x and y sweeps fused over tiles of a z plane, the fused kernel
-# reads Q^(k) and writes the accumulator (80 B) and the z sweep moves the
-# 186.7 B above.
-BYTES_PER_CELL_STAGE_3D_FUSED = 80.0 + 120.0 + 200.0 / 3.0
+# 3D (40 B per cell state): the plane kernel reads Q^(k) and writes the residual
+# accumulator (80 B); the column kernel reads Q^(k) and the accumulator, writes
+# the result and reads Q^n (stage 1) or Q^n and Q^(k) (stages 2, 3) for the
+# update: 120 + (40 + 80 + 80)/3 B.  Per cell-stage on average:
+BYTES_PER_CELL_STAGE_3D = 80.0 + 120.0 + 200.0 / 3.0
 SWEEPS3 = {"lines": 0, "fused": 1, "fused_half": 2}
 
 WORKLOADS = {
@@ -133,7 +128,7 @@ def parse():
     ap.add_argument("--calib-copy-mb", type=int, default=0,
                     help="run one device copy of this many MiB first (HBM counter calibration)")
     ap.add_argument("--sweeps3", default="lines", choices=sorted(SWEEPS3),
-                    help="3D launch form: line sweeps, or x/y fused over z-plane tiles")
+                    help="3D launch form (one pair of kernels serves every value)")
     ap.add_argument("--tiling", default="auto",
                     help="tile variant index, or 'auto' (gbr_autotune on the initial state)")
     return ap.parse_args()
@@ -551,20 +546,16 @@ def bench_3d(a, n):
 
 
 def bytes_3d(a):
-    return BYTES_PER_CELL_STAGE_3D if a.sweeps3 == "lines" else BYTES_PER_CELL_STAGE_3D_FUSED
+    return BYTES_PER_CELL_STAGE_3D
 
 
 def step_3d(a):
     dt = "dt (first step: reduction over Q^n; then from the stage-3 extrema)"
-    if a.sweeps3 == "lines":
-        return f"{dt} + 3 x (x, y, z line-sweep kernels)"
-    return f"{dt} + 3 x (x/y kernel over z-plane tiles + z line-sweep kernel)"
+    return f"{dt} + 3 x (x/y lines of z-plane tiles + z lines)"
 
 
 def kernel_3d(a):
-    if a.sweeps3 == "lines":
-        return "meg7_sweep3_kernel (x, y, z per stage)"
-    return "meg7_xy3_kernel + meg7_sweep3_kernel (z) per stage"
+    return "meg7_plane3_kernel + meg7_col3_kernel per stage"
 
 
 def timed3(a, P, s, order, steps):
@@ -632,13 +623,6 @@ def bench_3d_fixed(a, n, steps):
                      "avg_launch_us": stage_ms * 1e3, "bytes_per_cell_stage": bpc},
         "status": st,
     }
-    if not a.no_compare:
-        other = "lines" if a.sweeps3 != "lines" else "fused"
-        b = argparse.Namespace(**vars(a))
-        b.sweeps3 = other
-        ms2, stage2, st2 = timed3(b, P, s, 7, steps)
-        out["other_form"] = {"sweeps": other, "value": cells * 3 * steps / (ms2 * 1e-3),
-                             "ms_per_step": ms2 / steps, "stage_us": stage2 * 1e3, "status": st2}
     if not a.no_cpu_baseline:
         import oracle as O
         cfg = O.make_cfg3(n, n, n, *P.geometry(), bc=P.bc, gamma=P.gamma, order=7)

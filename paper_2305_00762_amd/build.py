@@ -14,8 +14,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgbr.so")
-SOURCES = ["gbr_api.hip", "batch.hip", "stage_fp64.hip", "stage_fp64_mlp.hip", "stage_f32.hip",
-           "stage_f32_mlp.hip", "stage_cons.hip", "stage_order4.hip", "stage_shock_stable.hip",
+SOURCES = ["gbr_api.hip", "batch.hip", "stage3d.hip", "stage_fp64.hip", "stage_fp64_mlp.hip",
+           "stage_f32.hip", "stage_f32_mlp.hip", "stage_cons.hip", "stage_order4.hip", "stage_shock_stable.hip",
            "stage_mpe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

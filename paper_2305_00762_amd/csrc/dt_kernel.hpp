@@ -10,12 +10,10 @@
 // in the status word, since fmin would otherwise drop a NaN.
 #pragma once
 #include "batch_kernel.hpp"
+#include "dt_kernel_common.hpp"
 #include "stage_kernel.hpp"
 
 namespace gbr {
-
-constexpr int kDtBlocks = 1024;  // pass-1 workgroups at most (partials kept in context scratch)
-constexpr int kDtThreads = 256;
 
 // Pass-1 workgroups for n cells: 1024 from 4M cells on, where more loads in
 // flight pay (-17% at 4096^2); 512 below, where the second pass's extra
@@ -34,18 +32,6 @@ struct DtParams {
   int nx, ny;
   double dx, dy, gamma, mu, cfl;
 };
-
-__device__ __forceinline__ double block_min(double v, double* red) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o));
-  const int w = threadIdx.x >> 6;
-  __syncthreads();
-  if (__lane_id() == 0) red[w] = v;
-  __syncthreads();
-  double r = red[0];
-  for (int k = 1; k < (int)(blockDim.x >> 6); ++k) r = fmin(r, red[k]);
-  return r;
-}
 
 // Convective and viscous limits of cell s folded into (conv, visc).
 __device__ __forceinline__ void dt_cell(const double* __restrict__ Q, size_t n, size_t s,

@@ -12,7 +12,7 @@
 #include "batch_kernel.hpp"
 #include "dt_kernel.hpp"
 #include "mlp_kernels.hpp"
-#include "stage3d.hpp"
+#include "stage3d_launch.hpp"
 #include "stage_variants.hpp"
 
 namespace {
@@ -1135,30 +1135,8 @@ int gbr_batch_autotune(gbr_batch* b, int reps, void* stream) {
 }  // extern "C"
 
 // ---------------------------------------------------------------------------
-// Three dimensions (inviscid): one line-sweep kernel per direction and stage.
-namespace {
-constexpr int k3NP = 32, k3NL = 8;   // positions per tile along the line, lines per workgroup
-using Sweep3Fn = void (*)(const Sweep3Params&, int, hipStream_t);
-template <int DIR, int ORD>
-void launch_sweep3(const Sweep3Params& P, int grid, hipStream_t s) {
-  hipLaunchKernelGGL((meg7_sweep3_kernel<DIR, k3NP, k3NL, ORD>), dim3(grid), dim3(256), 0, s, P);
-}
-const Sweep3Fn kSweep3[2][3] = {
-    {launch_sweep3<0, 7>, launch_sweep3<1, 7>, launch_sweep3<2, 7>},
-    {launch_sweep3<0, 4>, launch_sweep3<1, 4>, launch_sweep3<2, 4>}};
-// fused x/y forms: 15x15 tiles of a z plane, all 15 lines of a sweep at once
-// (two workgroups per CU) or 8 at a time (three)
-using XY3Fn = void (*)(const XY3Params&, int, hipStream_t);
-template <int NL, int ORD>
-void launch_xy3(const XY3Params& P, int grid, hipStream_t s) {
-  using C = XY3Cfg<15, 15, NL>;
-  static_assert(C::LDS_BYTES <= 160 * 1024, "LDS per workgroup");
-  hipLaunchKernelGGL((meg7_xy3_kernel<C, ORD>), dim3(grid), dim3(C::NT), 0, s, P);
-}
-const XY3Fn kXY3[2][2] = {{launch_xy3<15, 7>, launch_xy3<8, 7>},
-                          {launch_xy3<15, 4>, launch_xy3<8, 4>}};
-constexpr int kXY3T = 15;   // tile side of the fused forms
-}  // namespace
+// Three dimensions (inviscid): a plane kernel (x and y) and a column kernel (z)
+// per stage.
 
 struct gbr3_ctx {
   int n[3];
@@ -1166,7 +1144,6 @@ struct gbr3_ctx {
   double lo[3], hi[3];
   int bc[3];
   int order;
-  int sweeps;                 // GBR3_SWEEPS_*
   int device;
   int export_flags;
   unsigned* d_status;         // [4]
@@ -1190,10 +1167,8 @@ int gbr3_init(int nx, int ny, int nz, double gamma, gbr3_ctx** out) {
   c->n[0] = nx; c->n[1] = ny; c->n[2] = nz; c->gamma = gamma;
   for (int d = 0; d < 3; ++d) { c->lo[d] = 0.0; c->hi[d] = 1.0; c->bc[d] = GBR_BC_PERIODIC; }
   c->order = 7;
-  c->sweeps = GBR3_SWEEPS_LINES;
   const size_t n = (size_t)nx * ny * nz;
-  // the z sweep's workgroups: line groups of the xy plane x position tiles
-  const size_t zslots = 4 * (((size_t)nx * ny + k3NL - 1) / k3NL) * ((nz + k3NP - 1) / k3NP);
+  const size_t zslots = (size_t)col3_tiles(nx, ny, nz) * kCol3Waves;
   bool ok = hipGetDevice(&c->device) == hipSuccess &&
             hipMalloc(&c->d_status, 4 * sizeof(unsigned)) == hipSuccess &&
             hipMalloc(&c->d_partial, 3 * kDtBlocks * sizeof(double)) == hipSuccess &&
@@ -1244,8 +1219,7 @@ int gbr3_set_order(gbr3_ctx* c, int order) {
 
 int gbr3_set_sweeps(gbr3_ctx* c, int form) {
   if (!c || form < GBR3_SWEEPS_LINES || form > GBR3_SWEEPS_XY_FUSED_HALF) return GBR_EINVAL;
-  c->sweeps = form;
-  return GBR_OK;
+  return GBR_OK;   // one launch form serves them all
 }
 
 int gbr3_export_flags(gbr3_ctx* c, int enable) {
@@ -1302,45 +1276,20 @@ static int launch3(gbr3_ctx* c, int mode, const double* dt, const double* Qn, co
     c->ev_used += 2;
     if (hipEventRecord(tev[0], s) != hipSuccess) return GBR_EDEVICE;
   }
-  const int o4 = c->order == 4 ? 1 : 0;
-  const bool fused = c->sweeps != GBR3_SWEEPS_LINES;
-  if (fused) {
-    XY3Params X{};
-    X.Qk = Qk; X.R = c->d_R;
-    X.sigx = c->export_flags ? c->d_sig[0] : nullptr;
-    X.sigy = c->export_flags ? c->d_sig[1] : nullptr;
-    X.status = c->d_status;
-    X.nx = c->n[0]; X.ny = c->n[1]; X.nz = c->n[2]; X.bcx = c->bc[0]; X.bcy = c->bc[1];
-    X.tiles_x = (c->n[0] + kXY3T - 1) / kXY3T;
-    X.tiles_y = (c->n[1] + kXY3T - 1) / kXY3T;
-    const long long nt = (long long)X.tiles_x * X.tiles_y * c->n[2];
-    if (nt > 0x7fffffff) return GBR_EINVAL;
-    X.ntiles = (int)nt;
-    X.inv_dx = (double)c->n[0] / (c->hi[0] - c->lo[0]);
-    X.inv_dy = (double)c->n[1] / (c->hi[1] - c->lo[1]);
-    X.gamma = c->gamma; X.g1inv = 1.0 / (c->gamma - 1.0);
-    kXY3[o4][c->sweeps == GBR3_SWEEPS_XY_FUSED ? 0 : 1](X, X.ntiles, s);
+  Stage3Params P{};
+  P.Qk = Qk; P.Qn = Qn; P.R = c->d_R; P.out = out; P.dt = dt;
+  P.status = c->d_status;
+  P.nx = c->n[0]; P.ny = c->n[1]; P.nz = c->n[2];
+  for (int d = 0; d < 3; ++d) {
+    P.sig[d] = c->export_flags ? c->d_sig[d] : nullptr;
+    P.bc[d] = c->bc[d];
+    P.inv_d[d] = (double)c->n[d] / (c->hi[d] - c->lo[d]);
   }
-  for (int d = fused ? 2 : 0; d < 3; ++d) {
-    Sweep3Params P{};
-    P.Qk = Qk; P.Qn = Qn; P.R = c->d_R; P.out = out; P.dt = dt;
-    P.sig = c->export_flags ? c->d_sig[d] : nullptr;
-    P.status = c->d_status;
-    P.nx = c->n[0]; P.ny = c->n[1]; P.nz = c->n[2];
-    P.bc = c->bc[d];
-    P.inv_d = (double)c->n[d] / (c->hi[d] - c->lo[d]);
-    P.gamma = c->gamma; P.g1inv = 1.0 / (c->gamma - 1.0);
-    P.first = !fused && d == 0; P.last = d == 2;
-    P.mode = mode;
-    P.ptiles = (c->n[d] + k3NP - 1) / k3NP;
-    const long long lines = (long long)c->n[(d + 1) % 3] * c->n[(d + 2) % 3];
-    const long long groups = (lines + k3NL - 1) / k3NL;
-    const long long grid = groups * P.ptiles;
-    if (grid > 0x7fffffff) return GBR_EINVAL;
-    P.dtx = (d == 2 && mode == MODE_STAGE3) ? c->d_dtx : nullptr;
-    kSweep3[o4][d](P, (int)grid, s);
-    if (P.dtx) c->stage3_slots = (int)grid * 4;
-  }
+  P.gamma = c->gamma; P.g1inv = 1.0 / (c->gamma - 1.0);
+  P.mode = mode;
+  P.dtx = mode == MODE_STAGE3 ? c->d_dtx : nullptr;
+  launch_stage3(P, c->order, s);
+  if (P.dtx) c->stage3_slots = (int)(col3_tiles(P.nx, P.ny, P.nz) * kCol3Waves);
   if (tev && hipEventRecord(tev[1], s) != hipSuccess) return GBR_EDEVICE;
   return hip_ok(hipGetLastError());
 }
@@ -1370,7 +1319,7 @@ int gbr3_compute_dt(gbr3_ctx* c, const double* Q, double cfl, double* dt_dev, vo
   P.dz = (c->hi[2] - c->lo[2]) / c->n[2];
   P.gamma = c->gamma;
   const int blocks = dt_blocks((size_t)c->n[0] * c->n[1] * c->n[2]);
-  hipLaunchKernelGGL(dt3_reduce_kernel, dim3(blocks), dim3(kDtThreads), 0, s, P);
+  launch_dt3(P, blocks, s);
   hipLaunchKernelGGL(dt_finish_kernel, dim3(1), dim3(kDtThreads), 0, s, c->d_partial, blocks,
                      dt_dev, cfl, c->d_status);
   return hip_ok(hipGetLastError());
