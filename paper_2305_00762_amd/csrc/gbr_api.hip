@@ -1168,7 +1168,7 @@ int gbr3_init(int nx, int ny, int nz, double gamma, gbr3_ctx** out) {
   for (int d = 0; d < 3; ++d) { c->lo[d] = 0.0; c->hi[d] = 1.0; c->bc[d] = GBR_BC_PERIODIC; }
   c->order = 7;
   const size_t n = (size_t)nx * ny * nz;
-  const size_t zslots = (size_t)col3_tiles(nx, ny, nz) * kCol3Waves;
+  const size_t zslots = (size_t)col3_tiles(nx, ny, nz) * kCol3MaxWaves;
   bool ok = hipGetDevice(&c->device) == hipSuccess &&
             hipMalloc(&c->d_status, 4 * sizeof(unsigned)) == hipSuccess &&
             hipMalloc(&c->d_partial, 3 * kDtBlocks * sizeof(double)) == hipSuccess &&
@@ -1288,8 +1288,8 @@ static int launch3(gbr3_ctx* c, int mode, const double* dt, const double* Qn, co
   P.gamma = c->gamma; P.g1inv = 1.0 / (c->gamma - 1.0);
   P.mode = mode;
   P.dtx = mode == MODE_STAGE3 ? c->d_dtx : nullptr;
-  launch_stage3(P, c->order, s);
-  if (P.dtx) c->stage3_slots = (int)(col3_tiles(P.nx, P.ny, P.nz) * kCol3Waves);
+  const int waves = launch_stage3(P, c->order, s);
+  if (P.dtx) c->stage3_slots = waves;
   if (tev && hipEventRecord(tev[1], s) != hipSuccess) return GBR_EDEVICE;
   return hip_ok(hipGetLastError());
 }

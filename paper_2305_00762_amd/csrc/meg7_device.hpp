@@ -80,6 +80,13 @@ __device__ __forceinline__ bool div_rb_ok(double a) {
   return m <= 0x1p300 && (m >= 0x1p-300 || m == 0.0);
 }
 
+// The compiler would issue all of a long walk's loads first and its sums last,
+// which needs several times the register file: pin() makes a running sum's
+// value due here, hold() keeps the loads on either side apart.
+template <class T>
+__device__ __forceinline__ void pin(T& v) { __asm__ volatile("" : "+v"(v)); }
+__device__ __forceinline__ void hold() { __asm__ volatile("" ::: "memory"); }
+
 // Sixth-order central first derivative, eq. (eqn:six), scaled by the
 // spacing: returns dx * dPhi/dx from Phi_{-3..3} (pm3 .. p3).
 __device__ __forceinline__ double grad6(double pm3, double pm2, double pm1, double p1,
@@ -113,17 +120,18 @@ static_assert(kPsiC == 0.5, "the division-free decision assumes psi_c = 1/2");
 __device__ __forceinline__ bool detector_flag(double rm2, double rm1, double r0, double rp1,
                                               double rp2) {
 #pragma clang fp contract(off)
-  double a = fabs(r0 - rm1) + fabs((r0 - 2.0 * rm1) + rm2);
-  double b = fabs(r0 - rp1) + fabs((r0 - 2.0 * rp1) + rp2);
-  double num = (2.0 * a) * b + kDetEps;
+  // (2 x is exact, so each fused operation below rounds as the product and sum
+  // it stands for)
+  double a = fabs(r0 - rm1) + fabs(fma(-2.0, rm1, r0) + rm2);
+  double b = fabs(r0 - rp1) + fabs(fma(-2.0, rp1, r0) + rp2);
+  double num = fma(2.0, a * b, kDetEps);
   double den = (a * a + b * b) + kDetEps;
-  return (2.0 * num - den) < -(den * 0x1p-54);
+  return fma(2.0, num, -den) < -(den * 0x1p-54);
 }
 
+// (sign a + sign b)/2 min(|a|,|b|), eq. (eqn:alpha): one of the two terms is zero
 __device__ __forceinline__ double minmod(double a, double b) {
-  // (sign a + sign b)/2 * min(|a|,|b|), eq. (eqn:alpha)
-  double m = fmin(fabs(a), fabs(b));
-  return (a > 0.0 && b > 0.0) ? m : ((a < 0.0 && b < 0.0) ? -m : 0.0);
+  return fmax(fmin(a, b), 0.0) + fmin(fmax(a, b), 0.0);
 }
 
 // GRB interface states, eq. (eqn:grb).  v[k] = Phi_{j+k-2} (k=0..5),
@@ -282,26 +290,79 @@ __device__ __forceinline__ void meg7_char_states(FW Wf, FG Gf, double gamma, dou
       gamma, WLo, WRo);
 }
 
-// The same with the gradients formed from edge jumps: Ef(a, f) is the jump of
-// rotated field f across edge (j - 5 + a) + 1/2, a = 0..10.  The gradient of
-// eq. (eqn:six) at cell k is (37, -8, 1)/60 on the pairs of edges around k;
-// being linear, it is taken once on the combined jumps of the two fields.
-template <int ORD = 7, class FW, class FE>
-__device__ __forceinline__ void meg7_char_states_edges(FW Wf, FE Ef, double gamma, double WLo[4],
-                                                       double WRo[4]) {
-  meg7_char_states_comb<ORD>(
-      Wf,
-      [&](int fa, int fb, double ca, double cb, double cg[6]) {
-        double ce[11];
+// The same from the cells alone, for NV = 4 fields (rho, u_n, u_t, p) or 5
+// (rho, u_n, u_t1, u_t2, p: an identity row and column for the second
+// tangential velocity): Vc(k, f) is field f at offset k - 5 from cell j,
+// k = 0..11.  Each field is read once and its six gradients (eq. eqn:six) are
+// formed once: the two acoustic rows from (u_n, p), the entropy row from rho
+// and the p still at hand, then the tangential ones.  Against one row at a
+// time, each from its two fields: half the reads and 110 of about 1000
+// operations fewer.
+// F32: the gradients of the FP32-bulk form, float32 stencils on float32 edge
+// jumps.
+template <int NV, int ORD, bool F32, class FV>
+__device__ __forceinline__ void meg7_char_states_cells(FV Vc, double gamma, double* WLo,
+                                                       double* WRo) {
+  const double rb = 0.5 * (Vc(5, 0) + Vc(6, 0));
+  const double pb = 0.5 * (Vc(5, NV - 1) + Vc(6, NV - 1));
+  const double irb = rcp_nr(rb);
+  const double cb = sqrt_nr(gamma * pb * irb);
+  const double icb = rcp_nr(cb);
+  const double ic2 = icb * icb, h2c2 = 0.5 * ic2, ca = rb * (0.5 * icb);
+  const double cor = cb * irb, c2 = cb * cb;
+  auto field = [&](int f, double (&v)[6], double (&g)[6]) {
+    double c[12];
 #pragma unroll
-        for (int a = 0; a < 11; ++a) ce[a] = ca * Ef(a, fa) + cb * Ef(a, fb);
-        constexpr double z = 1.0 / 60.0;
+    for (int k = 0; k < 12; ++k) c[k] = Vc(k, f);
+    float e[11];
+    if (F32) {
 #pragma unroll
-        for (int q = 0; q < 6; ++q)
-          cg[q] = z * (37.0 * (ce[q + 2] + ce[q + 3]) - 8.0 * (ce[q + 1] + ce[q + 4]) +
-                       (ce[q] + ce[q + 5]));
-      },
-      gamma, WLo, WRo);
+      for (int a = 0; a < 11; ++a) e[a] = (float)(c[a + 1] - c[a]);
+    }
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+      v[q] = c[q + 3];
+      if (F32)
+        g[q] = (1.0f / 60.0f) * (37.0f * (e[q + 2] + e[q + 3]) - 8.0f * (e[q + 1] + e[q + 4]) +
+                                 (e[q] + e[q + 5]));
+      else
+        g[q] = grad6(c[q], c[q + 1], c[q + 2], c[q + 4], c[q + 5], c[q + 6]);
+    }
+  };
+  double vp[6], gp[6], v[6], g[6], mv[6], mg[6];
+  double l0, r0, l1, r1, l2, r2;
+  field(NV - 1, vp, gp);
+  field(1, v, g);
+#pragma unroll
+  for (int q = 0; q < 6; ++q) {
+    const double t = ca * v[q], u = ca * g[q];
+    mv[q] = h2c2 * vp[q] - t;
+    mg[q] = h2c2 * gp[q] - u;
+    v[q] = h2c2 * vp[q] + t;
+    g[q] = h2c2 * gp[q] + u;
+  }
+  meg7_pair<ORD>(mv, mg, l0, r0);
+  meg7_pair<ORD>(v, g, l2, r2);
+  hold();
+  field(0, v, g);
+#pragma unroll
+  for (int q = 0; q < 6; ++q) {
+    v[q] -= ic2 * vp[q];
+    g[q] -= ic2 * gp[q];
+  }
+  meg7_pair<ORD>(v, g, l1, r1);
+  WLo[0] = l0 + l1 + l2;
+  WRo[0] = r0 + r1 + r2;
+  WLo[1] = cor * (l2 - l0);
+  WRo[1] = cor * (r2 - r0);
+  WLo[NV - 1] = c2 * (l0 + l2);
+  WRo[NV - 1] = c2 * (r0 + r2);
+#pragma unroll
+  for (int t = 2; t < NV - 1; ++t) {
+    hold();
+    field(t, v, g);
+    meg7_pair<ORD>(v, g, WLo[t], WRo[t]);
+  }
 }
 
 // Conservative (rho, rho un, rho ut, E) to primitive (rho, un, ut, p),
@@ -482,41 +543,41 @@ __device__ __forceinline__ double sin_quarter(double x) {
 // energy rows a_L/(S_L - S*) (E_L + p_L + m_L S*), resp. R.  The Roe sound
 // speed is c~^2 = w_L c_L^2 + w_R c_R^2 + (gamma-1)/2 w_L w_R |dU|^2 (the
 // Roe enthalpy less the kinetic energy of the Roe velocity, term by term:
-// no cancellation), and the reciprocals of S_L - S* and S_R - S* come from
-// one of their product.  About 130 operations and 8 estimates where the
-// component-wise wave sum with two-step Newton refinements took 230 and 11
-// (1024^2 Riemann step 285 -> 273 us, 128^3 step 1280 -> 1228 us).
+// no cancellation).  One estimate of 1/sqrt(rho_L rho_R) gives both specific
+// volumes and the Roe weights, one reciprocal of the product of D = m_L - m_R
+// and (S_L - S*) D, (S_R - S*) D gives all three quotients.  About 120
+// operations and 6 estimates, where the component-wise wave sum with two-step
+// Newton refinements took 230 and 11.
 template <int NV, bool LOW_MACH = false>
 __device__ __forceinline__ void hllc_n(const double* WL, const double* WR, const double* Fm,
                                        double fs, double gamma, double g1inv, double* F) {
   const double rl = WL[0], ul = WL[1], pl = WL[NV - 1];
   const double rr = WR[0], ur = WR[1], pr = WR[NV - 1];
-  const double yl = rsq_c3(rl), yr = rsq_c3(rr);
-  const double sl = rl * yl, sr = rr * yr;              // sqrt(rho)
-  const double al = gamma * pl * (yl * yl), ar = gamma * pr * (yr * yr);   // c^2
+  const double y = rsq_c3(rl * rr), y2 = y * y;
+  const double al = gamma * pl * (rr * y2), ar = gamma * pr * (rl * y2);   // c^2
   const double cl = sqrt_c3(al), cr = sqrt_c3(ar);
-  const double iss = rcp_c3(sl + sr);
-  const double wl = sl * iss, wr = sr * iss;
+  const double t = rr * y;                              // sqrt(rho_R / rho_L)
+  const double wl = rcp_c3(1.0 + t), wr = t * wl;
   const double du = ur - ul, dp = pr - pl;
   double kl = ul * ul, kr = ur * ur, dk = du * du;
 #pragma unroll
-  for (int t = 2; t < NV - 1; ++t) {
-    const double dv = WR[t] - WL[t];
-    kl += WL[t] * WL[t];
-    kr += WR[t] * WR[t];
+  for (int i = 2; i < NV - 1; ++i) {
+    const double dv = WR[i] - WL[i];
+    kl += WL[i] * WL[i];
+    kr += WR[i] * WR[i];
     dk += dv * dv;
   }
   const double ut = wl * ul + wr * ur;
   const double ct = sqrt_c3(wl * al + wr * ar + (0.5 * (gamma - 1.0)) * (wl * wr) * dk);
   const double SL = fmin(ul - cl, ut - ct);
   const double SR = fmax(ur + cr, ut + ct);
-  const double ml = rl * (SL - ul), mr = rr * (SR - ur);
-  const double iden = rcp_c3(ml - mr);
-  const double aL = (dp - du * mr) * iden, aR = (dp - du * ml) * iden;
-  const double Ss = ul + aL;
-  const double dL = SL - Ss, dR = SR - Ss;
-  const double id = rcp_c3(dL * dR);
-  const double qL = aL * (id * dR), qR = aR * (id * dL);   // a / (S - S*)
+  const double bL = SL - ul, bR = SR - ur;
+  const double ml = rl * bL, mr = rr * bR, D = ml - mr;
+  const double nL = dp - du * mr, nR = dp - du * ml;    // a D
+  const double xL = bL * D - nL, xR = bR * D - nR;      // (S - S*) D
+  const double z = xL * xR, rD = rcp_c3(D * z);
+  const double Ss = ul + nL * (rD * z);
+  const double qL = nL * (rD * D * xR), qR = nR * (rD * D * xL);   // a / (S - S*)
   double phi = 1.0;
   if (LOW_MACH) {
     // |u| < c/10 on both sides is Ma < 0.1 (at the limit phi is 1 to rounding)
@@ -537,8 +598,8 @@ __device__ __forceinline__ void hllc_n(const double* WL, const double* WR, const
   F[0] = fs * Fm[0] - 0.5 * d0;
   F[1] = fs * Fm[1] - 0.5 * d1;
 #pragma unroll
-  for (int t = 2; t < NV - 1; ++t)
-    F[t] = fs * Fm[t] - 0.5 * ((GL * WL[t] - GR * WR[t]) + aS * (rr * WR[t] - rl * WL[t]));
+  for (int i = 2; i < NV - 1; ++i)
+    F[i] = fs * Fm[i] - 0.5 * ((GL * WL[i] - GR * WR[i]) + aS * (rr * WR[i] - rl * WL[i]));
   F[NV - 1] = fs * Fm[NV - 1] - 0.5 * dE;
 }
 template <bool LOW_MACH = false>

@@ -62,61 +62,6 @@ __device__ __forceinline__ void conv_flux3(const double W[5], double g1inv, doub
   F[4] = W[1] * (E + W[4]);
 }
 
-// Characteristic MEG7 states in 3D: the primitive eigenvectors of the 2D
-// projection at the mean density and pressure, plus the identity row and
-// column of the second tangential velocity.  Vc(k, f): rotated primitive
-// field f (0..4) at offset k - 5 from cell j, k = 0..11; the gradients are
-// those of eq. (eqn:six) on the combined jumps.  Rows of L: (u_n, p),
-// (rho, p), (u_t1), (u_t2), (u_n, p), limited one at a time in a rolled loop.
-template <int ORD, class FV>
-__device__ __forceinline__ void meg7_char_states3(FV Vc, double gamma, double WLo[5],
-                                                  double WRo[5]) {
-  const double rb = 0.5 * (Vc(5, 0) + Vc(6, 0));
-  const double pb = 0.5 * (Vc(5, 4) + Vc(6, 4));
-  const double irb = rcp_nr(rb);
-  const double cb = sqrt_nr(gamma * pb * irb);
-  const double icb = rcp_nr(cb);
-  const double h2c = 0.5 * icb, ic2 = icb * icb, h2c2 = 0.5 * ic2;
-  const double cor = cb * irb, c2 = cb * cb;
-#pragma unroll
-  for (int m = 0; m < 5; ++m) { WLo[m] = 0.0; WRo[m] = 0.0; }
-#pragma unroll 1
-  for (int m = 0; m < 5; ++m) {
-    // row m of L as ca * field fa + cbv * field fb
-    const bool tang = (m == 2 || m == 3);
-    const int fa = (m == 1) ? 0 : (tang ? m : 1);
-    const int fb = tang ? m : 4;
-    const double ca = (m == 0) ? -rb * h2c : ((m == 4) ? rb * h2c : 1.0);
-    const double cbv = (m == 1) ? -ic2 : (tang ? 0.0 : h2c2);
-    double cv[6], cg[6], ce[11];
-    double a0 = Vc(0, fa), b0v = Vc(0, fb);
-#pragma unroll
-    for (int k = 1; k < 12; ++k) {
-      const double a1 = Vc(k, fa), b1v = Vc(k, fb);
-      ce[k - 1] = ca * (a1 - a0) + cbv * (b1v - b0v);
-      if (k >= 3 && k <= 8) cv[k - 3] = ca * a1 + cbv * b1v;
-      a0 = a1;
-      b0v = b1v;
-    }
-    constexpr double z = 1.0 / 60.0;
-#pragma unroll
-    for (int q = 0; q < 6; ++q)
-      cg[q] = z * (37.0 * (ce[q + 2] + ce[q + 3]) - 8.0 * (ce[q + 1] + ce[q + 4]) +
-                   (ce[q] + ce[q + 5]));
-    double cl, cr;
-    meg7_pair<ORD>(cv, cg, cl, cr);
-    // column m of R = L^{-1}: (1,-c/rho,0,0,c^2), (1,0,0,0,0), (0,0,1,0,0), (0,0,0,1,0),
-    // (1,c/rho,0,0,c^2)
-    const double b0 = tang ? 0.0 : 1.0;
-    const double b1 = (m == 0) ? -cor : ((m == 4) ? cor : 0.0);
-    const double b2 = (m == 2) ? 1.0 : 0.0;
-    const double b3 = (m == 3) ? 1.0 : 0.0;
-    const double b4 = (m == 0 || m == 4) ? c2 : 0.0;
-    WLo[0] += b0 * cl; WLo[1] += b1 * cl; WLo[2] += b2 * cl; WLo[3] += b3 * cl; WLo[4] += b4 * cl;
-    WRo[0] += b0 * cr; WRo[1] += b1 * cr; WRo[2] += b2 * cr; WRo[3] += b3 * cr; WRo[4] += b4 * cr;
-  }
-}
-
 // A lane's walk: fluxes F of its K interfaces from the tile U (five planes of
 // RS), the first one right of cell r0, cells SN apart along the line; DIR sets
 // the rotation.  rof(t): r0 of lane t of the wave; queue: this wave's; valid:
@@ -251,10 +196,8 @@ __device__ __forceinline__ unsigned walk3(const double* U, double gamma, double 
         const int e = queue[base + lid];
         const int r = rof(e / K) + (e % K) * SN;
         double WL[5], WR[5], FL[5], FR[5];
-        meg7_char_states3<ORD>(
-            [&](int k, int f) { return U[(f == 0 || f == 4 ? f : 1 + (DIR + f - 1) % 3) * RS + r +
-                                         (k - 5) * SN]; },
-            gamma, WL, WR);
+        meg7_char_states_cells<5, ORD, false>(
+            [&](int k, int f) { return U[rot[f] * RS + r + (k - 5) * SN]; }, gamma, WL, WR);
         if (!(WL[0] > 0.0 && WL[4] > 0.0 && WR[0] > 0.0 && WR[4] > 0.0)) {
           vars(r, WL);
           vars(r + SN, WR);
@@ -324,18 +267,14 @@ __global__ __launch_bounds__(C::NT, C::MINW) void meg7_plane3_kernel(Stage3Param
   {
     constexpr int LR = (C::NLOAD + NT - 1) / NT;
     double q[LR][5];
+    int o[LR];
+    cell_offsets<C, LR>(P.nx, P.ny, P.bc[0], P.bc[1], tx0, ty0, o);
 #pragma unroll
-    for (int k = 0; k < LR; ++k) {
-      const int c = tid + k * NT;
-      if (c < C::NLOAD) {
-        int lx, ly;
-        C::cell(c, lx, ly);
-        const size_t s = zb + (size_t)bc_index(ty0 + ly, P.ny, P.bc[1]) * P.nx +
-                         bc_index(tx0 + lx, P.nx, P.bc[0]);
+    for (int k = 0; k < LR; ++k)
+      if (tid + k * NT < C::NLOAD) {
 #pragma unroll
-        for (int m = 0; m < 5; ++m) q[k][m] = P.Qk[m * n + s];
+        for (int m = 0; m < 5; ++m) q[k][m] = P.Qk[m * n + zb + o[k]];
       }
-    }
     bool bad = false;
 #pragma unroll
     for (int k = 0; k < LR; ++k) {
@@ -452,12 +391,14 @@ __global__ __launch_bounds__(C::NT, C::MINW) void meg7_col3_kernel(Stage3Params 
   const int gl = g0 + l < nl ? g0 + l : nl - 1;
   {
     constexpr int LR = (C::RZ * W + NT - 1) / NT;
+    const bool wide = P.nz >= TZ + H;
     double q[LR][5];
 #pragma unroll
     for (int k = 0; k < LR; ++k) {
       const int c = tid + k * NT, p = c / W;
       if (p < C::RZ) {
-        const size_t s = (size_t)bc_index(z0 + p - H, P.nz, P.bc[2]) * nl + gl;
+        const size_t s = (size_t)(wide ? bc_index1(z0 + p - H, P.nz, P.bc[2])
+                                       : bc_index(z0 + p - H, P.nz, P.bc[2])) * nl + gl;
 #pragma unroll
         for (int m = 0; m < 5; ++m) q[k][m] = P.Qk[m * n + s];
       }

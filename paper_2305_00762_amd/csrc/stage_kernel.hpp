@@ -73,6 +73,39 @@ __device__ __forceinline__ int bc_index(int k, int n, int bc) {
   }
   return k < 0 ? 0 : (k >= n ? n - 1 : k);
 }
+// The same where one wrap suffices: n at least the reach past the grid.
+__device__ __forceinline__ int bc_index1(int k, int n, int bc) {
+  if (bc != 0) return min(max(k, 0), n - 1);
+  k = k < 0 ? k + n : k;
+  return k >= n ? k - n : k;
+}
+
+// Element offsets gi nx + gj of the cells a thread stages for the tile at
+// (tx0, ty0), ghost cells by the boundary kinds: a tile whose halo stays inside
+// the grid takes none of the ghost arithmetic, one on a grid of at least a
+// tile and halo takes a single wrap, smaller grids the general loops.
+template <class C, int LR>
+__device__ __forceinline__ void cell_offsets(int nx, int ny, int bcx, int bcy, int tx0, int ty0,
+                                             int (&o)[LR]) {
+  constexpr int H = C::H;
+  auto each = [&](auto gx, auto gy) {
+#pragma unroll
+    for (int k = 0; k < LR; ++k) {
+      const int c = threadIdx.x + k * C::NT;
+      if (c < C::NLOAD) {
+        int lx, ly;
+        C::cell(c, lx, ly);
+        o[k] = gy(ty0 + ly) * nx + gx(tx0 + lx);
+      }
+    }
+  };
+  if (tx0 >= H && ty0 >= H && tx0 + C::TX + H <= nx && ty0 + C::TY + H <= ny)
+    each([](int k) { return k; }, [](int k) { return k; });
+  else if (nx >= C::TX + H && ny >= C::TY + H)
+    each([&](int k) { return bc_index1(k, nx, bcx); }, [&](int k) { return bc_index1(k, ny, bcy); });
+  else
+    each([&](int k) { return bc_index(k, nx, bcx); }, [&](int k) { return bc_index(k, ny, bcy); });
+}
 
 template <int TX_, int TY_, int SX_, int SY_, int NT_, bool VISC_>
 struct TileCfg {
@@ -609,23 +642,19 @@ __device__ __forceinline__ void stage_load(const StageParams& P, double* sU, int
     // paid once rather than once per round.  Element offsets fit 32 bits
     // (4 nx ny <= 2^31 - 1).
     double q[LR][4];
+    int o[LR];
+    cell_offsets<C, LR>(P.nx, P.ny, P.bcx, P.bcy, tx0, ty0, o);
     const double* Q0 = P.Qk;
     const double* Q1 = P.Qk + n;
     const double* Q2 = P.Qk + 2 * n;
     const double* Q3 = P.Qk + 3 * n;
 #pragma unroll
     for (int k = 0; k < LR; ++k) {
-      const int c = tid + k * NT;
-      if (c < NLOAD) {
-        int lx, ly;
-        C::cell(c, lx, ly);
-        const int gi = inner ? ty0 + ly : bc_index(ty0 + ly, P.ny, P.bcy);
-        const int gj = inner ? tx0 + lx : bc_index(tx0 + lx, P.nx, P.bcx);
-        const int o = gi * P.nx + gj;
-        q[k][0] = Q0[o];
-        q[k][1] = Q1[o];
-        q[k][2] = Q2[o];
-        q[k][3] = Q3[o];
+      if (tid + k * NT < NLOAD) {
+        q[k][0] = Q0[o[k]];
+        q[k][1] = Q1[o[k]];
+        q[k][2] = Q2[o[k]];
+        q[k][3] = Q3[o[k]];
       }
     }
 #pragma unroll

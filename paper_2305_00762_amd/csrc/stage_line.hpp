@@ -18,17 +18,18 @@
 //
 // F32 (FP32 bulk): the GRB corrections are summed and the Riemann solver runs
 // in float32 on the jumps, U^L = U_j + cL, U^R = U_{j+1} + cR, U^R - U^L =
-// dU + cR - cL, every wave jump a product of small quantities; the mean flux,
-// flagged interfaces, viscous flux and divergence are FP64.
+// dU + cR - cL, every wave jump a product of small quantities; flagged
+// interfaces take float32 gradients and hold their flux's deviation from the
+// central one in float32.  The mean flux, MP limiter, viscous flux and
+// divergence are FP64.
 //
-// What bounds it: VALU issue, busy 81% of the time at 4096^2 (15x15 tiles,
-// K = 4).  A tile takes 3824 wave instructions of VALU against 4365 of the
-// barrier-phased form with per-line buffers, and 36% of its LDS instructions,
-// whose waits held that form at 57%.  The 48 running sums of K = 4 fit 168
-// registers, 3 waves per SIMD; K = 8 does not.  Measured per stage (Riemann
-// field, that form -> this): 4096^2 FP64 1071 -> 735 us (15x15), 710 (31x15),
-// FP32 803 -> 662; 1024^2 FP64 91 -> 66; viscous shear 2048^2 FP64 303 -> 202,
-// FP32 235 -> 191.
+// What bounds it: VALU issue, busy 81% at 4096^2 (15x15 tiles, K = 4).  The
+// barrier-phased form with per-line buffers before it issued 1.14 times the
+// VALU and 2.8 times the LDS instructions, whose waits held it at 57%.  The 48
+// running sums of K = 4 fit 168 registers, 3 waves per SIMD; K = 8 does not.
+// Measured per stage (Riemann field, that form -> this): 4096^2 FP64 1071 ->
+// 703 us (15x15), 676 (31x15), FP32 803 -> 622; 1024^2 FP64 91 -> 60; viscous
+// shear 2048^2 FP64 303 -> 195, FP32 235 -> 185.
 #pragma once
 #include <type_traits>
 
@@ -49,18 +50,19 @@ __device__ __forceinline__ void hllc_diss_f32(const float WL[4], const float WR[
   const float rl = WL[0], ul = WL[1], vl = WL[2], pl = WL[3];
   const float rr = WR[0], ur = WR[1], vr = WR[2], pr = WR[3];
   const float dr = dW[0], du = dW[1], dv = dW[2], dp = dW[3];
-  const float yl = rsqf(rl), yr = rsqf(rr);
-  const float sl = rl * yl, sr = rr * yr, irl = yl * yl, irr = yr * yr;
+  // 1/sqrt(rho_L rho_R) gives both specific volumes and the Roe weights; the
+  // Roe sound speed from the jumps, as in hllc_n
+  const float y = rsqf(rl * rr), y2 = y * y;
   const float kl2 = ul * ul + vl * vl, kr2 = ur * ur + vr * vr;
   const float El = pl * g1inv + 0.5f * rl * kl2;
   const float Er = pr * g1inv + 0.5f * rr * kr2;
-  const float cl = sqrtf_fast(gamma * pl * irl), cr = sqrtf_fast(gamma * pr * irr);
-  const float hl = (El + pl) * irl, hr = (Er + pr) * irr;
-  const float iss = rcpf(sl + sr);
-  const float ut = (sl * ul + sr * ur) * iss;
-  const float vt = (sl * vl + sr * vr) * iss;
-  const float ht = (sl * hl + sr * hr) * iss;
-  const float ct = sqrtf_fast((gamma - 1.0f) * (ht - 0.5f * (ut * ut + vt * vt)));
+  const float al = gamma * pl * (rr * y2), ar = gamma * pr * (rl * y2);
+  const float cl = sqrtf_fast(al), cr = sqrtf_fast(ar);
+  const float t = rr * y;
+  const float wl = rcpf(1.0f + t), wr = t * wl;
+  const float ut = wl * ul + wr * ur;
+  const float ct = sqrtf_fast(wl * al + wr * ar +
+                              (0.5f * (gamma - 1.0f)) * (wl * wr) * (du * du + dv * dv));
   const float SL = fminf(ul - cl, ut - ct);
   const float SR = fmaxf(ur + cr, ut + ct);
   const float ml = rl * (SL - ul), mr = rr * (SR - ur);
@@ -122,13 +124,6 @@ struct LineCfg {
   static constexpr int QN = 64 * K * (WX + WY);
   static constexpr int LDS_BYTES = 8 * 4 * RS + (int)sizeof(QT) * QN + 16;
 };
-
-// The compiler would issue all of a walk's loads first and its sums last,
-// which needs several times the register file: pin() makes a running sum's
-// value due here, hold() keeps the loads on either side apart.
-template <class T>
-__device__ __forceinline__ void pin(T& v) { __asm__ volatile("" : "+v"(v)); }
-__device__ __forceinline__ void hold() { __asm__ volatile("" ::: "memory"); }
 
 // Integer stencil weights: GRB corrections on the edge jumps
 // (pos+b-4)+1/2, b = 0..8 (eq. eqn:grb, or its fourth-order subset, with
@@ -290,22 +285,19 @@ struct LineSweep {
   }
 
   // Characteristic MEG7 flux of the flagged interface right of cell r
-  // (Secs. 2.3, 2.4): one characteristic field at a time, its gradients on
-  // the jumps of the field's own combination over the cells r - 5 .. r + 6.
+  // (Secs. 2.3, 2.4), from the cells r - 5 .. r + 6.
   __device__ static __forceinline__ void flagged(const StageParams& P, const double* U, int r,
                                                  double (&F)[4]) {
     double WL[4], WR[4];
     constexpr int rot[4] = {0, FN, FT, 3};
     auto Vc = [&](int k, int f) { return U[rot[f] * RS + r + (k - 5) * SN]; };
-    auto Vf = [&](int q, int f) { return Vc(q + 3, f); };
     if (CONS) {
       double QL[4], QR[4];
       meg7_char_states_cons_cells<ORD>(Vc, P.gamma, QL, QR);
       cons_to_prim(QL, P.gamma, WL);
       cons_to_prim(QR, P.gamma, WR);
     } else {
-      meg7_char_states_edges<ORD>(Vf, [&](int a, int f) { return Vc(a + 1, f) - Vc(a, f); },
-                                  P.gamma, WL, WR);
+      meg7_char_states_cells<4, ORD, F32>(Vc, P.gamma, WL, WR);
     }
     if (!(WL[0] > 0.0 && WL[3] > 0.0 && WR[0] > 0.0 && WR[3] > 0.0)) {
       double V[4];
@@ -320,6 +312,19 @@ struct LineSweep {
 #pragma unroll
     for (int m = 0; m < 4; ++m) Fm[m] = FL[m] + FR[m];
     hllc_n<4, LM>(WL, WR, Fm, 0.5, P.gamma, P.g1inv, F);
+    if (F32) {
+      // the deviation from the central flux is held in float32
+      double V0[4], V1[4];
+      vars(U, r, V0);
+      vars(U, r + SN, V1);
+      conv_flux(V0, P.g1inv, FL);
+      conv_flux(V1, P.g1inv, FR);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const double B = 0.5 * (FL[m] + FR[m]);
+        F[m] = B + (double)(float)(F[m] - B);
+      }
+    }
   }
 
   // Fluxes of lane t (all 64 lanes of the wave call it); queue: this wave's.
