@@ -565,6 +565,7 @@ int gbr_stage_dt(gbr_ctx* c, double cfl, double* dt_dev, void* stream) {
 // Learned detector.
 static constexpr int kMlpMaxBatch = 1 << 16;
 static constexpr int kMlpMaxBlocks = kMlpMaxBatch / 256;
+static_assert(kMlpWideBatch / 64 <= kMlpMaxBlocks, "partials of the one-group form");
 
 int gbr_mlp_create(gbr_mlp** out) {
   if (!out) return GBR_EINVAL;
@@ -636,9 +637,8 @@ int gbr_mlp_features(gbr_ctx* c, const double* Q, uint16_t* feat, uint8_t* chi, 
   MlpFeatParams P{};
   P.Q = Q; P.feat = feat; P.chi = chi;
   P.nx = c->nx; P.ny = c->ny; P.bcx = c->bcx; P.bcy = c->bcy; P.gamma = c->gamma;
-  const size_t n = (size_t)c->nx * c->ny;   // one thread per cell, both directions
-  hipLaunchKernelGGL(mlp_features_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                     (hipStream_t)stream, P);
+  const int blocks = ((c->nx + kFeatTX - 1) / kFeatTX) * ((c->ny + kFeatTY - 1) / kFeatTY);
+  hipLaunchKernelGGL(mlp_features_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)stream, P);
   return hip_ok(hipGetLastError());
 }
 
@@ -657,9 +657,11 @@ int gbr_mlp_grad(gbr_mlp* m, const uint16_t* feat, const uint8_t* labels, const 
   MlpGradParams P;
   P.M = mlp_image(m);
   P.feat = feat; P.label = labels; P.idx = idx; P.batch = batch; P.partial = m->d_partial;
-  const int nblk = (batch + 255) / 256;
-  hipLaunchKernelGGL(mlp_grad_kernel, dim3(nblk), dim3(256), 0, s, P);
-  hipLaunchKernelGGL(mlp_sum_kernel, dim3((kMlpNP + 1 + 255) / 256), dim3(256), 0, s,
+  const bool wide = batch <= kMlpWideBatch;   // at most kMlpMaxBlocks workgroups either way
+  const int cells = wide ? 64 : 256, nblk = (batch + cells - 1) / cells;
+  if (wide) hipLaunchKernelGGL(mlp_grad_kernel<1>, dim3(nblk), dim3(256), 0, s, P);
+  else hipLaunchKernelGGL(mlp_grad_kernel<4>, dim3(nblk), dim3(256), 0, s, P);
+  hipLaunchKernelGGL(mlp_sum_kernel, dim3((kMlpNP + 1 + 63) / 64), dim3(1024), 0, s,
                      (const float*)m->d_partial, nblk, grad);
   return hip_ok(hipGetLastError());
 }

@@ -8,9 +8,15 @@
 //   plane: 15x15 tiles of a z plane with a 6-cell halo in x and y, x lines and
 //          y lines on different waves at the same time; writes the residual
 //          accumulator R = -dF/dx - dG/dy (40 B per cell read, 40 written);
-//   column: kColW consecutive cells of the xy plane x 15 cells along z with the
+//   column: kCol3W consecutive cells of the xy plane x 15 cells along z with the
 //          halo along z; adds -dH/dz and stores the residual or the SSP-RK3
 //          stage (eq. rk).
+// The plane kernel is bound by VALU issue (busy 86% on the 128^3 Taylor-Green
+// field, 132 us; 158 us on the octant Riemann field, where 8% of the interfaces
+// take the shock branch), the column kernel by memory (84 us for the 200 B a
+// cell-stage moves there, 5 TB/s; 98 on the Riemann field).  One barrier-phased
+// kernel per direction, with staged gradients and fluxes in LDS, took 126 + 141
+// + 159 us on that Riemann field.
 #pragma once
 #include "dt_kernel_common.hpp"
 #include "meg7_device.hpp"
