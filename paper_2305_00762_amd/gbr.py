@@ -176,6 +176,34 @@ def _addr(x):
 
 # grid sizes of live contexts, for the size checks: handle -> (nx, ny[, nz])
 _dims = {}
+# torch's device-tensor type and element types, and its current stream as a raw
+# handle; filled on first use (a stage call passes four tensors and a stream, and
+# on a small grid the checks would otherwise cost as much as the launch)
+_torch = None
+
+
+def _lazy_torch():
+    global _torch
+    try:
+        import torch
+    except ImportError:      # host arrays and raw addresses still pass
+        _torch = (None, {}, None)
+        return _torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+    def current():
+        return raw(torch._C._cuda_getDevice())
+
+    def first():             # initialises torch's runtime, as current_stream does
+        global _torch
+        stream = torch.cuda.current_stream().cuda_stream
+        if raw is not None:
+            _torch = _torch[:2] + (current,)
+        return stream
+
+    _torch = (torch.Tensor, {n: getattr(torch, n) for n in ("float64", "float32", "int32", "int16",
+                                                            "uint8")}, first)
+    return _torch
 
 
 def _bad(where, what):
@@ -187,6 +215,11 @@ def _dev(x, where, name, dtypes, numel, exact=False, optional=False, host_ok=Fal
     tensor on the HIP device (or, with host_ok, a host array), contiguous, of
     one of the element types `dtypes` (names, e.g. "float64"), with numel
     elements (at least numel unless exact).  Raw integers pass unchecked."""
+    tensor, types, _ = _torch or _lazy_torch()
+    if type(x) is tensor and x.is_cuda and x.dtype is types[dtypes[0]] and x.is_contiguous():
+        n = x.numel()
+        if n == numel or (n > numel and not exact):
+            return x.data_ptr()
     if x is None:
         if optional:
             return None
@@ -221,10 +254,7 @@ def _cells(ctx, where):
     d = _dims.get(ctx)
     if d is None:
         _bad(where, "unknown or destroyed context")
-    n = 1
-    for v in d:
-        n *= v
-    return n
+    return d[0] * d[1] if len(d) == 2 else d[0] * d[1] * d[2]
 
 
 def _state(ctx, x, where, name, nvar=4, optional=False):
@@ -238,8 +268,10 @@ def _scalar(x, where, name, dtype="float64", optional=False, host_ok=False):
 
 def _stream(s):
     if s is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        current = (_torch or _lazy_torch())[2]
+        if current is None:
+            raise ImportError("a stream of None needs torch (pass a raw hipStream_t)")
+        return current()
     if isinstance(s, int):
         return s
     return s.cuda_stream
