@@ -21,6 +21,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # multiply-adds fuse as the source groups them, so one tile function
+         # rounds alike in every kernel it is inlined into
+         "-ffp-contract=on",
          # matrix-core results in VGPRs (no accumulator-register copies)
          "-mllvm", "-amdgpu-mfma-vgpr-form=1",
          "-Wall", "-Wno-unused-function", "-I", os.path.join(ROOT, "include")]

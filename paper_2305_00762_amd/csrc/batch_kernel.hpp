@@ -62,7 +62,7 @@ __global__ __launch_bounds__(CI::NT, CI::MINW) void meg7_batch_kernel(BatchParam
                     CI::QN == CV::QN,
                 "one tile shape");
   __shared__ double sU[4 * CI::RS];
-  __shared__ typename CI::QT sQueue[CI::QN];
+  __shared__ unsigned short sQueue[CI::QN];
   const int G = gridDim.x, b = blockIdx.x;
   const int xcd = b & 7, per = G >> 3;   // G is a multiple of 8
   for (int base = 0; base < B.total; base += G) {

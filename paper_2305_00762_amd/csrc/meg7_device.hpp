@@ -112,21 +112,25 @@ __device__ __forceinline__ double detector_psi(double rm2, double rm1, double r0
 // num = 2ab + eps and den = a^2 + b^2 + eps as above (both positive),
 // fl(num / den) < 1/2 holds exactly when num / den < 1/2 - 2^-55 (the rounding
 // boundary below 1/2; a tie rounds to 1/2, whose significand is even), i.e.
-// when 2 num - den < -den 2^-54.  2 num is exact, 2 num - den is exact
-// wherever the two are within a factor 2 of each other (Sterbenz) and has the
-// sign that decides otherwise, and den 2^-54 is exact: the comparison below
-// is the division's decision bit for bit, for a fraction of its cost.
+// when den - 2 num > den 2^-54.  That is 2 num < den: let 2^e <= 2 num < 2^(e+1)
+// be below den.  Where den < 2^(e+2) both are multiples of 2^(e-52), so
+// den - 2 num >= 2^(e-52) > den 2^-54; where den >= 2^(e+2), den - 2 num >
+// den / 2.  And 2 num = fl(4 ab + 2 eps) (scaling by 2 is exact), one fused
+// operation on fl(ab).
+// em, ep: the density jumps r0 - rm1 and rp1 - r0.
 static_assert(kPsiC == 0.5, "the division-free decision assumes psi_c = 1/2");
+__device__ __forceinline__ bool detector_flag_jumps(double rm2, double rm1, double r0, double rp1,
+                                                    double rp2, double em, double ep) {
+#pragma clang fp contract(off)
+  double a = fabs(em) + fabs(fma(-2.0, rm1, r0) + rm2);
+  double b = fabs(ep) + fabs(fma(-2.0, rp1, r0) + rp2);
+  double den = (a * a + b * b) + kDetEps;
+  return fma(4.0, a * b, 2.0 * kDetEps) < den;
+}
 __device__ __forceinline__ bool detector_flag(double rm2, double rm1, double r0, double rp1,
                                               double rp2) {
 #pragma clang fp contract(off)
-  // (2 x is exact, so each fused operation below rounds as the product and sum
-  // it stands for)
-  double a = fabs(r0 - rm1) + fabs(fma(-2.0, rm1, r0) + rm2);
-  double b = fabs(r0 - rp1) + fabs(fma(-2.0, rp1, r0) + rp2);
-  double num = fma(2.0, a * b, kDetEps);
-  double den = (a * a + b * b) + kDetEps;
-  return fma(2.0, num, -den) < -(den * 0x1p-54);
+  return detector_flag_jumps(rm2, rm1, r0, rp1, rp2, r0 - rm1, rp1 - r0);
 }
 
 // (sign a + sign b)/2 min(|a|,|b|), eq. (eqn:alpha): one of the two terms is zero

@@ -72,18 +72,20 @@ __device__ __forceinline__ void conv_flux3(const double W[5], double g1inv, doub
 // RS), the first one right of cell r0, cells SN apart along the line; DIR sets
 // the rotation.  rof(t): r0 of lane t of the wave; queue: this wave's; valid:
 // how many of the K interfaces exist.  All 64 lanes of the wave call it.
-// Returns the flags, bit q set where interface q takes the shock branch.
-template <int DIR, int K, int RS, int SN, int ORD, class QT, class RO>
-__device__ __forceinline__ unsigned walk3(const double* U, double gamma, double g1inv, QT* queue,
-                                          int r0, int valid, RO rof, double (&F)[K][5]) {
+// Returns the flags, bit q set where the detector flags interface q.
+template <int DIR, int K, int RS, int SN, int ORD, class RO>
+__device__ __forceinline__ unsigned walk3(const double* U, double gamma, double g1inv,
+                                          unsigned short* queue, int r0, int valid, RO rof,
+                                          double (&F)[K][5]) {
   const int lid = threadIdx.x & 63;
   constexpr int rot[5] = {0, 1 + DIR % 3, 1 + (DIR + 1) % 3, 1 + (DIR + 2) % 3, 4};
   auto vars = [&](int r, double (&V)[5]) {
 #pragma unroll
     for (int m = 0; m < 5; ++m) V[m] = U[rot[m] * RS + r];
   };
-  double Fm[K][5], cL[K][5], cR[K][5], pv[5], rw[5], nv[5];
-  bool flag[K];
+  double Fm[K][5], cL[K][5], cR[K][5], pv[5], rw[5], re[3], nv[5];
+  bool flag[K], first[K];
+  unsigned bits = 0;
 #pragma unroll
   for (int q = 0; q < K; ++q) flag[q] = false;
   vars(r0 - 4 * SN, nv);
@@ -124,10 +126,13 @@ __device__ __forceinline__ unsigned walk3(const double* U, double gamma, double 
 #pragma unroll
     for (int a = 0; a < 4; ++a) rw[a] = rw[a + 1];
     rw[4] = V[0];
+    re[0] = re[1];
+    re[1] = re[2];
+    re[2] = rw[4] - rw[3];
     if (c >= 4) {
       // the detector at cell r0 + (c - 6) SN feeds the interfaces within reach
       const int o = c - 6;
-      const bool chi = detector_flag(rw[0], rw[1], rw[2], rw[3], rw[4]);
+      const bool chi = detector_flag_jumps(rw[0], rw[1], rw[2], rw[3], rw[4], re[0], re[1]);
 #pragma unroll
       for (int q = 0; q < K; ++q)
         if (o >= q - 2 && o <= q + 3) flag[q] = flag[q] | chi;
@@ -156,42 +161,33 @@ __device__ __forceinline__ unsigned walk3(const double* U, double gamma, double 
       WL[m] = VL[m] + s * cL[q][m];
       WR[m] = VR[m] + s * cR[q][m];
     }
-    if (!(WL[0] > 0.0 && WL[4] > 0.0 && WR[0] > 0.0 && WR[4] > 0.0)) {
-      // unphysical reconstruction: first-order states and fluxes
-      double f0[5], f1[5];
-      conv_flux3(VL, g1inv, f0);
-      conv_flux3(VR, g1inv, f1);
-#pragma unroll
-      for (int m = 0; m < 5; ++m) {
-        WL[m] = VL[m];
-        WR[m] = VR[m];
-        Fm[q][m] = (0.5 * flux_den<ORD>()) * (f0[m] + f1[m]);
-      }
-    }
+    // an unphysical reconstruction joins the queue for first-order states
+    const bool ok = WL[0] > 0.0 && WL[4] > 0.0 && WR[0] > 0.0 && WR[4] > 0.0;
     hllc_n<5>(WL, WR, Fm[q], fs, gamma, g1inv, F[q]);
 #pragma unroll
     for (int m = 0; m < 5; ++m) pin(F[q][m]);
 #pragma unroll
     for (int m = 0; m < 5; ++m) VL[m] = VR[m];
-    flag[q] = flag[q] && q < valid;
+    if (flag[q] && q < valid) bits |= 1u << q;
+    first[q] = q < valid && !flag[q] && !ok;
+    flag[q] = q < valid && (flag[q] || !ok);
     hold();
   }
 
-  // flagged interfaces, compacted within the wave
+  // interfaces outside the smooth branch, compacted within the wave
   int slot[K], nq = 0;
-  unsigned bits = 0;
   const unsigned long long below = (1ull << lid) - 1ull;
 #pragma unroll
   for (int q = 0; q < K; ++q) {
     const unsigned long long ball = __ballot(flag[q]);
     slot[q] = nq + (int)__popcll(ball & below);
     nq += (int)__popcll(ball);
-    if (flag[q]) bits |= 1u << q;
   }
   if (nq) {
 #pragma unroll
     for (int q = 0; q < K; ++q)
-      if (flag[q]) queue[slot[q]] = (QT)(lid * K + q);
+      if (flag[q])
+        queue[slot[q]] = (unsigned short)((lid * K + q) | (first[q] ? kFirstOrder : 0u));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -199,11 +195,14 @@ __device__ __forceinline__ unsigned walk3(const double* U, double gamma, double 
     for (int base = 0; base < nq; base += 64) {
       double G[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
       if (base + lid < nq) {
-        const int e = queue[base + lid];
+        const unsigned code = queue[base + lid];
+        const int e = code & (kFirstOrder - 1);
         const int r = rof(e / K) + (e % K) * SN;
         double WL[5], WR[5], FL[5], FR[5];
-        meg7_char_states_cells<5, ORD, false>(
-            [&](int k, int f) { return U[rot[f] * RS + r + (k - 5) * SN]; }, gamma, WL, WR);
+        WL[0] = -1.0;
+        if (!(code & kFirstOrder))
+          meg7_char_states_cells<5, ORD, false>(
+              [&](int k, int f) { return U[rot[f] * RS + r + (k - 5) * SN]; }, gamma, WL, WR);
         if (!(WL[0] > 0.0 && WL[4] > 0.0 && WR[0] > 0.0 && WR[4] > 0.0)) {
           vars(r, WL);
           vars(r + SN, WR);
@@ -259,7 +258,7 @@ template <class C, int ORD>
 __global__ __launch_bounds__(C::NT, C::MINW) void meg7_plane3_kernel(Stage3Params P) {
   constexpr int RS = C::RS, RX = C::RX, H = C::H, NT = C::NT, K = C::K, TX = C::TX, TY = C::TY;
   __shared__ double sU[5 * RS];
-  __shared__ typename C::QT sQueue[C::QN];
+  __shared__ unsigned short sQueue[C::QN];
   const int tile = tile3();
   if (tile >= P.ntiles) return;
   const int tpp = P.tiles_x * P.tiles_y;
@@ -301,7 +300,7 @@ __global__ __launch_bounds__(C::NT, C::MINW) void meg7_plane3_kernel(Stage3Param
   int line, seg;
   bool act;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  typename C::QT* queue = sQueue + 64 * K * wave;
+  unsigned short* queue = sQueue + 64 * K * wave;
   auto sweep = [&](auto dir) {
     using L = LineSweep<C, decltype(dir)::value, false, false, ORD, false, false>;
     const int t = tid - (L::X ? 0 : 64 * C::WX);
@@ -376,14 +375,13 @@ struct Col3Cfg {
   static_assert(SG * K <= TZ + 2, "segments stay inside the halo");
   static constexpr int NT = SG * W;
   static_assert(NT % 64 == 0, "whole waves");
-  using QT = typename std::conditional<(64 * K <= 256), unsigned char, unsigned short>::type;
 };
 
 template <class C, int ORD>
 __global__ __launch_bounds__(C::NT, C::MINW) void meg7_col3_kernel(Stage3Params P) {
   constexpr int RS = C::RS, W = C::W, TZ = C::TZ, H = C::H, NT = C::NT, K = C::K;
   __shared__ double sU[5 * RS];
-  __shared__ typename C::QT sQueue[C::NT * K];
+  __shared__ unsigned short sQueue[C::NT * K];
   const int tile = tile3();
   if (tile >= P.ntiles) return;
   // z tiles of one column group run one after the other on an XCD: they share

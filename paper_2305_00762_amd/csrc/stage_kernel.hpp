@@ -629,8 +629,8 @@ __device__ __forceinline__ void stage_load(const StageParams& P, double* sU, int
     // the state check covers the tile's own cells (a branch, so waves that
     // stage only halo cells skip it)
     if (lx >= 0 && lx < TX && ly >= 0 && ly < TY && tx0 + lx < P.nx && ty0 + ly < P.ny) {
-      if (!(r > 0.0 && p > 0.0 && isfinite(E) && isfinite(mx) && isfinite(my) && isfinite(r)))
-        bad = true;
+      // (a momentum that is not finite makes p negative or NaN)
+      if (!(r > 0.0 && p > 0.0 && isfinite(E) && isfinite(r))) bad = true;
     }
   };
   // a tile whose halo stays inside the grid needs no ghost rules

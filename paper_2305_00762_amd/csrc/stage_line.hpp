@@ -29,7 +29,11 @@
 // running sums of K = 4 fit 168 registers, 3 waves per SIMD; K = 8 does not.
 // Measured per stage (Riemann field, that form -> this): 4096^2 FP64 1071 ->
 // 703 us (15x15), 676 (31x15), FP32 803 -> 622; 1024^2 FP64 91 -> 60; viscous
-// shear 2048^2 FP64 303 -> 195, FP32 235 -> 185.
+// shear 2048^2 FP64 303 -> 195, FP32 235 -> 185.  Unphysical smooth states go
+// through the same per-wave queue as flagged interfaces (kFirstOrder): their
+// first-order fallback inline held registers and split every interface in
+// blocks; a step of the 1280x640 MEG7-cons tube took 212 us with it, 193
+// without (it spilled 24 registers, now 2), of 1024^2 FP64 186 and 183.
 #pragma once
 #include <type_traits>
 
@@ -39,7 +43,6 @@ namespace gbr {
 
 __device__ __forceinline__ float rcpf(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ float rsqf(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ float sqrtf_fast(float x) { return x * __builtin_amdgcn_rsqf(x); }
 
 // HLLC (Einfeldt bounds) dissipation |S_L|(Q*_L-Q_L) + |S*|(Q*_R-Q*_L) +
 // |S_R|(Q_R-Q*_R) from the left/right primitive states and their jump
@@ -57,14 +60,14 @@ __device__ __forceinline__ void hllc_diss_f32(const float WL[4], const float WR[
   const float El = pl * g1inv + 0.5f * rl * kl2;
   const float Er = pr * g1inv + 0.5f * rr * kr2;
   const float al = gamma * pl * (rr * y2), ar = gamma * pr * (rl * y2);
-  const float cl = sqrtf_fast(al), cr = sqrtf_fast(ar);
   const float t = rr * y;
   const float wl = rcpf(1.0f + t), wr = t * wl;
   const float ut = wl * ul + wr * ur;
-  const float ct = sqrtf_fast(wl * al + wr * ar +
-                              (0.5f * (gamma - 1.0f)) * (wl * wr) * (du * du + dv * dv));
-  const float SL = fminf(ul - cl, ut - ct);
-  const float SR = fmaxf(ur + cr, ut + ct);
+  const float at = wl * al + wr * ar +
+                   (0.5f * (gamma - 1.0f)) * (wl * wr) * (du * du + dv * dv);
+  const float yt = rsqf(at);   // c = a / sqrt(a)
+  const float SL = fminf(fmaf(-al, rsqf(al), ul), fmaf(-at, yt, ut));
+  const float SR = fmaxf(fmaf(ar, rsqf(ar), ur), fmaf(at, yt, ut));
   const float ml = rl * (SL - ul), mr = rr * (SR - ur);
   const float iden = rcpf(ml - mr);
   const float aL = (dp - du * mr) * iden;   // S* - u_L
@@ -89,6 +92,10 @@ __device__ __forceinline__ void hllc_diss_f32(const float WL[4], const float WR[
   diss[2] = (GL * vl - GR * vr) + aSS * dQ[2];
   diss[3] = (HL - HR) + aSS * dQ[3];
 }
+
+// Queue bit of an interface whose smooth reconstruction is unphysical: it takes
+// first-order states and their physical fluxes.
+constexpr unsigned kFirstOrder = 0x8000u;
 
 template <int TX_, int TY_, int K_, bool VISC_, int MINW_>
 struct LineCfg {
@@ -120,9 +127,9 @@ struct LineCfg {
       ly += ly < H ? -H : TY - H;
     }
   }
-  using QT = typename std::conditional<(64 * K <= 256), unsigned char, unsigned short>::type;
+  // queue entries: K lane + q, and kFirstOrder
   static constexpr int QN = 64 * K * (WX + WY);
-  static constexpr int LDS_BYTES = 8 * 4 * RS + (int)sizeof(QT) * QN + 16;
+  static constexpr int LDS_BYTES = 8 * 4 * RS + 2 * QN + 16;
 };
 
 // Integer stencil weights: GRB corrections on the edge jumps
@@ -284,20 +291,24 @@ struct LineSweep {
     }
   }
 
-  // Characteristic MEG7 flux of the flagged interface right of cell r
-  // (Secs. 2.3, 2.4), from the cells r - 5 .. r + 6.
+  // Flux of the interface right of cell r outside the smooth branch: the
+  // characteristic MEG7 states (Secs. 2.3, 2.4) from the cells r - 5 .. r + 6,
+  // or the two cells' states where those are unphysical or first is set.
   __device__ static __forceinline__ void flagged(const StageParams& P, const double* U, int r,
-                                                 double (&F)[4]) {
+                                                 bool first, double (&F)[4]) {
     double WL[4], WR[4];
     constexpr int rot[4] = {0, FN, FT, 3};
     auto Vc = [&](int k, int f) { return U[rot[f] * RS + r + (k - 5) * SN]; };
-    if (CONS) {
-      double QL[4], QR[4];
-      meg7_char_states_cons_cells<ORD>(Vc, P.gamma, QL, QR);
-      cons_to_prim(QL, P.gamma, WL);
-      cons_to_prim(QR, P.gamma, WR);
-    } else {
-      meg7_char_states_cells<4, ORD, F32>(Vc, P.gamma, WL, WR);
+    WL[0] = -1.0;
+    if (!first) {
+      if (CONS) {
+        double QL[4], QR[4];
+        meg7_char_states_cons_cells<ORD>(Vc, P.gamma, QL, QR);
+        cons_to_prim(QL, P.gamma, WL);
+        cons_to_prim(QR, P.gamma, WR);
+      } else {
+        meg7_char_states_cells<4, ORD, F32>(Vc, P.gamma, WL, WR);
+      }
     }
     if (!(WL[0] > 0.0 && WL[3] > 0.0 && WR[0] > 0.0 && WR[3] > 0.0)) {
       double V[4];
@@ -330,7 +341,7 @@ struct LineSweep {
   // Fluxes of lane t (all 64 lanes of the wave call it); queue: this wave's.
   // Returns whether the lane has interfaces of the tile.
   __device__ static __forceinline__ bool run(const StageParams& P, const double* U,
-                                             typename C::QT* queue, const unsigned char* chif,
+                                             unsigned short* queue, const unsigned char* chif,
                                              int t, int tx0, int ty0, double (&F)[K][4],
                                              int& line, int& p0) {
     const int wave0 = t & ~63, lid = t & 63;
@@ -343,9 +354,9 @@ struct LineSweep {
     const int r0 = ridx(line, j0);
 
     // ---- the walk over cells j0 - 4 .. j0 + K + 4 --------------------------
-    double Fm[K][4], pv[4], rw[5], nv[4];
+    double Fm[K][4], pv[4], rw[5], re[3], nv[4];
     RT cL[K][4], cR[K][4];
-    bool flag[K];
+    bool flag[K], first[K];
     vars(U, r0 - 4 * SN, nv);
 #pragma unroll
     for (int q = 0; q < K; ++q) flag[q] = false;
@@ -388,6 +399,9 @@ struct LineSweep {
 #pragma unroll
         for (int a = 0; a < 4; ++a) rw[a] = rw[a + 1];
         rw[4] = V[0];
+        re[0] = re[1];
+        re[1] = re[2];
+        re[2] = rw[4] - rw[3];
       }
       if (c >= 4) {
         // the detector at cell j0 + o feeds the interfaces q with o in [q-2, q+3]
@@ -396,7 +410,7 @@ struct LineSweep {
         if (DETMLP)
           chi = (chif[mlp_chi_index<C>(X ? j0 + o : line, X ? line : j0 + o)] >> DIR) & 1;
         else
-          chi = detector_flag(rw[0], rw[1], rw[2], rw[3], rw[4]);
+          chi = detector_flag_jumps(rw[0], rw[1], rw[2], rw[3], rw[4], re[0], re[1]);
 #pragma unroll
         for (int q = 0; q < K; ++q)
           if (o >= q - 2 && o <= q + 3) flag[q] = flag[q] | chi;
@@ -428,6 +442,7 @@ struct LineSweep {
           P.sigy[(size_t)(gi + 1) * P.nx + gj] = !flag[q];
       }
       vars(U, r0 + (q + 1) * SN, VR);
+      bool ok;
       constexpr double fs = 1.0 / flux_den<ORD>();
       if constexpr (F32) {
         float WL[4], WR[4], dW[4], diss[4];
@@ -439,56 +454,38 @@ struct LineSweep {
           WR[m] = (float)VR[m] + s * cR[q][m];
           dW[m] = e + s * (cR[q][m] - cL[q][m]);
         }
-        if (!(WL[0] > 0.f && WL[3] > 0.f && WR[0] > 0.f && WR[3] > 0.f)) {
-          double f0[4], f1[4];
-          conv_flux(VL, P.g1inv, f0);
-          conv_flux(VR, P.g1inv, f1);
-#pragma unroll
-          for (int m = 0; m < 4; ++m) {
-            WL[m] = (float)VL[m];
-            WR[m] = (float)VR[m];
-            dW[m] = (float)(VR[m] - VL[m]);
-            Fm[q][m] = (0.5 * flux_den<ORD>()) * (f0[m] + f1[m]);
-          }
-        }
+        ok = WL[0] > 0.f && WL[3] > 0.f && WR[0] > 0.f && WR[3] > 0.f;
         hllc_diss_f32(WL, WR, dW, (float)P.gamma, (float)P.g1inv, diss);
 #pragma unroll
         for (int m = 0; m < 4; ++m) F[q][m] = fs * Fm[q][m] - (double)(0.5f * diss[m]);
       } else {
-            double WL[4], WR[4];
-      constexpr double s = 1.0 / grb_den<ORD>();
+        double WL[4], WR[4];
+        constexpr double s = 1.0 / grb_den<ORD>();
 #pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        WL[m] = VL[m] + s * cL[q][m];
-        WR[m] = VR[m] + s * cR[q][m];
+        for (int m = 0; m < 4; ++m) {
+          WL[m] = VL[m] + s * cL[q][m];
+          WR[m] = VR[m] + s * cR[q][m];
+        }
+        if (CONS) {
+          const double QL[4] = {WL[0], WL[1], WL[2], WL[3]};
+          const double QR[4] = {WR[0], WR[1], WR[2], WR[3]};
+          cons_to_prim(QL, P.gamma, WL);
+          cons_to_prim(QR, P.gamma, WR);
+        }
+        ok = WL[0] > 0.0 && WL[3] > 0.0 && WR[0] > 0.0 && WR[3] > 0.0;
+        hllc_n<4, LM>(WL, WR, Fm[q], fs, P.gamma, P.g1inv, F[q]);
       }
-      if (CONS) {
-        const double QL[4] = {WL[0], WL[1], WL[2], WL[3]};
-        const double QR[4] = {WR[0], WR[1], WR[2], WR[3]};
-        cons_to_prim(QL, P.gamma, WL);
-        cons_to_prim(QR, P.gamma, WR);
-      }
-      if (!(WL[0] > 0.0 && WL[3] > 0.0 && WR[0] > 0.0 && WR[3] > 0.0)) {
-        // unphysical reconstruction: first-order states and fluxes
-        double f0[4], f1[4];
-        prims(VL, P.gamma, WL);
-        prims(VR, P.gamma, WR);
-        conv_flux(WL, P.g1inv, f0);
-        conv_flux(WR, P.g1inv, f1);
-#pragma unroll
-        for (int m = 0; m < 4; ++m) Fm[q][m] = (0.5 * flux_den<ORD>()) * (f0[m] + f1[m]);
-      }
-      hllc_n<4, LM>(WL, WR, Fm[q], fs, P.gamma, P.g1inv, F[q]);
-      }
+      // an unphysical reconstruction joins the queue for first-order states
+      first[q] = in && !flag[q] && !ok;
+      flag[q] = in && (flag[q] || !ok);
 #pragma unroll
       for (int m = 0; m < 4; ++m) pin(F[q][m]);
 #pragma unroll
       for (int m = 0; m < 4; ++m) VL[m] = VR[m];
-      flag[q] = flag[q] && in;
       hold();
     }
 
-    // ---- flagged interfaces, compacted within the wave ---------------------
+    // ---- interfaces outside the smooth branch, compacted within the wave ----
     int slot[K], nq = 0;
     const unsigned long long below = (1ull << lid) - 1ull;
 #pragma unroll
@@ -500,7 +497,8 @@ struct LineSweep {
     if (nq) {
 #pragma unroll
       for (int q = 0; q < K; ++q)
-        if (flag[q]) queue[slot[q]] = (typename C::QT)(lid * K + q);
+        if (flag[q])
+          queue[slot[q]] = (unsigned short)((lid * K + q) | (first[q] ? kFirstOrder : 0u));
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -508,10 +506,11 @@ struct LineSweep {
       for (int base = 0; base < nq; base += 64) {
         double G[4] = {0.0, 0.0, 0.0, 0.0};
         if (base + lid < nq) {
-          const int e = queue[base + lid];
+          const unsigned code = queue[base + lid];
+          const int e = code & (kFirstOrder - 1);
           int ln, sg;
           lane(wave0 + e / K, ln, sg);
-          flagged(P, U, ridx(ln, sg * K + e % K - 1), G);
+          flagged(P, U, ridx(ln, sg * K + e % K - 1), (code & kFirstOrder) != 0, G);
         }
         // each flux back to the lane that owns the interface
 #pragma unroll
@@ -534,7 +533,7 @@ struct LineSweep {
 // One tile of the stage.  sU: [4][RS]; queue: C::QN entries.
 template <class C, bool DETMLP, bool CONS, int ORD, bool LM, bool F32>
 __device__ __forceinline__ void stage_tile_line(const StageParams& P, int tx0, int ty0, double* sU,
-                                                typename C::QT* queue, unsigned char* sChiF) {
+                                                unsigned short* queue, unsigned char* sChiF) {
   constexpr int RS = C::RS, K = C::K;
   ChiMap<C> cm;
   if (DETMLP) fetch_chimap<C>(P, cm, tx0, ty0);
@@ -584,7 +583,7 @@ __device__ __forceinline__ void stage_tile_line(const StageParams& P, int tx0, i
 template <class C, bool DETMLP, bool CONS, int ORD, bool LM, bool F32 = false>
 __global__ __launch_bounds__(C::NT, C::MINW) void meg7_line_kernel(StageParams P) {
   __shared__ double sU[4 * C::RS];
-  __shared__ typename C::QT sQueue[C::QN];
+  __shared__ unsigned short sQueue[C::QN];
   __shared__ unsigned char sChiF[DETMLP ? (C::TX + 6) * (C::TY + 6) : 1];
   int tx0, ty0;
   if (!tile_origin(P, C::TX, C::TY, tx0, ty0)) return;
