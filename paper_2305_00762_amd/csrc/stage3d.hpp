@@ -298,23 +298,24 @@ __global__ __launch_bounds__(C::NT, C::MINW) void meg7_plane3_kernel(Stage3Param
 
   double F[K][5];
   int line, seg;
-  bool act;
+  bool act = false;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   unsigned short* queue = sQueue + 64 * K * wave;
   auto sweep = [&](auto dir) {
     using L = LineSweep<C, decltype(dir)::value, false, false, ORD, false, false>;
-    const int t = tid - (L::X ? 0 : 64 * C::WX);
-    L::lane(t, line, seg);
-    act = t < L::NLINES * L::SG;
+    const L sw(min(TX, P.nx - tx0), min(TY, P.ny - ty0));
+    const int wave0 = 64 * (wave - (L::X ? 0 : C::WX)), t = wave0 + (tid & 63);
+    act = t < sw.lanes;
+    if (wave0 >= sw.lanes) return;
+    sw.lane(t, line, seg);
     if (!act) line = seg = 0;
     const int p0 = seg * K;
-    const int valid = act ? (L::N + 1 - p0 < K ? L::N + 1 - p0 : K) : 0;
-    const int wave0 = t & ~63;
+    const int valid = act ? (sw.n + 1 - p0 < K ? sw.n + 1 - p0 : K) : 0;
     const unsigned bits = walk3<decltype(dir)::value, K, RS, L::SN, ORD>(
         sU, P.gamma, P.g1inv, queue, L::ridx(line, p0 - 1), valid,
         [&](int e) {
           int ln, sg;
-          L::lane(wave0 + e, ln, sg);
+          sw.lane(wave0 + e, ln, sg);
           return L::ridx(ln, sg * K - 1);
         },
         F);
@@ -338,7 +339,7 @@ __global__ __launch_bounds__(C::NT, C::MINW) void meg7_plane3_kernel(Stage3Param
   __syncthreads();   // every read of the tile is done: it becomes the flux buffer
   {
     const bool xw = wave < C::WX;
-    const int N = xw ? TX : TY;
+    const int N = xw ? min(TX, P.nx - tx0) : min(TY, P.ny - ty0);
     double* f = sU + (xw ? line * C::FX : C::FY0 + line * C::FY) + seg * K;
 #pragma unroll
     for (int q = 0; q < K; ++q)
@@ -416,8 +417,10 @@ __global__ __launch_bounds__(C::NT, C::MINW) void meg7_col3_kernel(Stage3Params 
   __syncthreads();
   double F[K][5];
   const int p0 = tid / W * K;
-  const int valid = TZ + 1 - p0 < K ? TZ + 1 - p0 : K;
-  {
+  const int vz = min(TZ, P.nz - z0);   // the tile's cells inside the grid
+  const int valid = vz + 1 - p0 < K ? vz + 1 - p0 : K;
+  // (waves past the last interface skip the walk)
+  if ((tid & ~63) / W * K <= vz) {
     const int wave0 = tid & ~63;
     const unsigned bits = walk3<2, K, RS, W, ORD>(
         sU, P.gamma, P.g1inv, sQueue + wave0 * K, (p0 - 1 + H) * W + l, valid,
