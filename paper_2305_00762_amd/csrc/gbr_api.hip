@@ -1170,7 +1170,7 @@ int gbr3_init(int nx, int ny, int nz, double gamma, gbr3_ctx** out) {
   for (int d = 0; d < 3; ++d) { c->lo[d] = 0.0; c->hi[d] = 1.0; c->bc[d] = GBR_BC_PERIODIC; }
   c->order = 7;
   const size_t n = (size_t)nx * ny * nz;
-  const size_t zslots = (size_t)col3_tiles(nx, ny, nz) * kCol3MaxWaves;
+  const size_t zslots = (size_t)col3_tiles(nx, ny, nz) * kCol3Waves;
   bool ok = hipGetDevice(&c->device) == hipSuccess &&
             hipMalloc(&c->d_status, 4 * sizeof(unsigned)) == hipSuccess &&
             hipMalloc(&c->d_partial, 3 * kDtBlocks * sizeof(double)) == hipSuccess &&

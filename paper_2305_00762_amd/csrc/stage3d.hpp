@@ -5,18 +5,19 @@
 // (x: v, w; y: w, u; z: u, v).  A stage is two kernels of the line-streamed form
 // (stage_line.hpp: a lane owns K consecutive interfaces of a line and walks the
 // K + 9 cells they span once, in registers, from an LDS tile of primitives):
-//   plane: 15x15 tiles of a z plane with a 6-cell halo in x and y, x lines and
-//          y lines on different waves at the same time; writes the residual
-//          accumulator R = -dF/dx - dG/dy (40 B per cell read, 40 written);
+//   plane: tiles of a z plane (15x15, 16x16 or 20x17) with a 6-cell halo in x
+//          and y, x lines and y lines on different waves at the same time;
+//          writes the residual accumulator R = -dF/dx - dG/dy (40 B per cell
+//          read, 40 written);
 //   column: kCol3W consecutive cells of the xy plane x 15 cells along z with the
 //          halo along z; adds -dH/dz and stores the residual or the SSP-RK3
 //          stage (eq. rk).
-// The plane kernel is bound by VALU issue (busy 86% on the 128^3 Taylor-Green
-// field, 132 us; 158 us on the octant Riemann field, where 8% of the interfaces
-// take the shock branch), the column kernel by memory (84 us for the 200 B a
-// cell-stage moves there, 5 TB/s; 98 on the Riemann field).  One barrier-phased
-// kernel per direction, with staged gradients and fluxes in LDS, took 126 + 141
-// + 159 us on that Riemann field.
+// The plane kernel is bound by VALU issue (151 us on the octant Riemann field
+// of 128^3, where 14% of the interfaces take the shock branch; 158 with 15x15
+// tiles and two interfaces a lane), the column kernel by memory (92 us there
+// for the 200 B a cell-stage moves, 4.6 TB/s; 98 with 32 lines).  One
+// barrier-phased kernel per direction, with staged gradients and fluxes in
+// LDS, took 126 + 141 + 159 us on that field.
 #pragma once
 #include "dt_kernel_common.hpp"
 #include "meg7_device.hpp"
@@ -251,9 +252,6 @@ __device__ __forceinline__ int tile3() {
 
 // ---------------------------------------------------------------------------
 // x and y lines of a z plane.
-template <int K, int MINW>
-using Plane3Cfg = LineCfg<15, 15, K, false, MINW>;
-
 template <class C, int ORD>
 __global__ __launch_bounds__(C::NT, C::MINW) void meg7_plane3_kernel(Stage3Params P) {
   constexpr int RS = C::RS, RX = C::RX, H = C::H, NT = C::NT, K = C::K, TX = C::TX, TY = C::TY;
@@ -367,7 +365,7 @@ __global__ __launch_bounds__(C::NT, C::MINW) void meg7_plane3_kernel(Stage3Param
 
 // ---------------------------------------------------------------------------
 // z lines: W consecutive cells of the xy plane (lines) x TZ cells along z.
-// Lanes run across the lines, so every LDS access is 32 consecutive doubles.
+// Lanes run across the lines, so every LDS access is W consecutive doubles.
 template <int W_, int TZ_, int K_, int MINW_>
 struct Col3Cfg {
   static constexpr int W = W_, TZ = TZ_, K = K_, MINW = MINW_, H = 6;
