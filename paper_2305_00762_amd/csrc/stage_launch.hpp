@@ -16,20 +16,32 @@ int launch_line_cfg(const StageParams& P, hipStream_t s) {
 }
 
 // Interfaces per lane by the number of tiles.  K = 4 reads and forms each cell
-// 3.25 times per interface where K = 1 does it 10 times, but leaves a 15x15
-// tile two waves: where the tiles do not fill the chip the serial chain of a
-// lane counts, and a tile's work is spread over more lanes.  Measured per
-// stage, us (Riemann field, K = 1 / 4 on 15x15 tiles, K = 2 / 4 on 31x15):
-//   64^2    12.2 / 22.3    18.7 / 26.5
-//   256^2   15.8 / 24.9    18.2 / 25.0
-//   400^2   20.6 / 26.8    29.4 / 34.2   (729 and 351 tiles)
-//   512^2   29.0 / 32.3    35.8 / 33.9   (1225 and 595 tiles; shear 24.1 / 20.8, 28.8 / 20.8)
-//   1024^2  80.8 / 65.7    104.3 / 68.8
-constexpr int kFewTiles15 = 1024, kFewTiles31 = 448;
+// 3.25 times per interface where K = 2 does it 5.5 and K = 1 ten times, but
+// leaves a 15x15 tile two waves: where the tiles do not fill the chip the serial
+// chain of a lane counts, and a tile's work is spread over more lanes.  The
+// viscous flux shares its walk between a lane's interfaces, so K = 1 does not
+// pay there.  Measured per stage, us (K = 1, 2, 4 on 15x15 tiles; K = 2, 4 on
+// 31x15):
+//                 Riemann                          shear layer (viscous)
+//   256^2    13.9 14.6 18.8   14.5 18.7       11.9 10.5 14.6   10.4 11.3
+//   350^2    17.8 17.2 19.4   20.8 21.4       (576 tiles of 15x15)
+//   400^2    18.8 20.2 20.9   23.5 26.3       16.8 13.8 15.6   19.0 15.7   (729, 351)
+//   450^2    22.7 21.6 21.3   26.2 26.8       (900, 450)
+//   512^2    25.9 23.9 25.4   30.6 26.8       24.7 19.1 19.7   27.5 20.1   (1225, 595)
+//   600^2    31.6 28.8 30.5   38.1 33.2       (1600, 800)
+//   700^2    40.6 36.1 34.8   50.6 36.4       40.7 30.7 31.1   46.2 30.3   (2209, 1081)
+//   1024^2   76.0 64.2 56.6   93.9 59.5       79.8 59.3 54.1   89.9 53.3
+// MEG7-cons needs more registers than four waves per SIMD leave, so its K = 1
+// ends earlier (K = 1, 2; 15x15): 128^2 16.4 19.1, 256^2 21.8 23.7 (324 tiles),
+// 400^2 35.2 28.9.
+constexpr int kFewTiles15 = 800, kFewTilesCons = 400, kMidTiles15 = 1900, kFewTiles31 = 448;
 template <bool VISC, bool MLP, bool F32 = false, bool CONS = false, int ORD = 7, bool LM = false>
 int launch_line15(const StageParams& P, hipStream_t s) {
-  if (P.ntiles < kFewTiles15)
-    return launch_line_cfg<LineCfg<15, 15, 1, VISC, CONS ? 3 : 4>, MLP, CONS, ORD, LM, F32>(P, s);
+  if constexpr (!VISC)
+    if (P.ntiles < (CONS ? kFewTilesCons : kFewTiles15))
+      return launch_line_cfg<LineCfg<15, 15, 1, VISC, CONS ? 3 : 4>, MLP, CONS, ORD, LM, F32>(P, s);
+  if (P.ntiles < kMidTiles15)
+    return launch_line_cfg<LineCfg<15, 15, 2, VISC, 3>, MLP, CONS, ORD, LM, F32>(P, s);
   return launch_line_cfg<LineCfg<15, 15, 4, VISC, 3>, MLP, CONS, ORD, LM, F32>(P, s);
 }
 template <bool VISC, bool MLP, bool F32 = false, bool CONS = false, int ORD = 7, bool LM = false>
