@@ -1,13 +1,15 @@
-// CFL time step of Sec. 2.5, reduced on the device in two passes.
+// CFL time step of Sec. 2.5, reduced on the device.
 //
 // Per cell: conv = min(dx/(|u|+c), dy/(|v|+c)) and visc = min(dx^2/nu, dy^2/nu)
 // (nu = mu/rho), each evaluated with one rounding per operation and IEEE
-// division / square root.  Pass 1: every workgroup reduces its cells to one
-// (conv, visc) pair in a fixed grid-stride pattern; pass 2: one workgroup
-// reduces the pairs and writes dt = cfl * min(visc / alpha_v, conv).  A min
-// is exact, so the result is bit-identical to any other evaluation order; no
-// atomics are used.  A bad cell (non-finite, rho <= 0, p <= 0) is recorded
-// in the status word, since fmin would otherwise drop a NaN.
+// division / square root.  Every workgroup reduces its cells to one (conv, visc)
+// pair in a fixed grid-stride pattern; on small grids the last workgroup to
+// finish reduces the pairs and writes dt = cfl * min(visc / alpha_v, conv), on
+// others a second launch does.  A min is exact, so the result is bit-identical
+// to any other evaluation order.  A bad cell (non-finite, rho <= 0, p <= 0) is
+// recorded in the status word, since fmin would otherwise drop a NaN.  The
+// entry point without a context keeps its scratch clear of counters and takes
+// two launches.
 #pragma once
 #include "batch_kernel.hpp"
 #include "dt_kernel_common.hpp"
@@ -24,9 +26,27 @@ inline int dt_blocks(size_t n) {
   return (int)(want < cap ? want : cap);
 }
 
+// A context's status words, then the arrival counts: one for the step of a state
+// and one for that of stage-3 extrema (their launches differ in size, and a
+// count is its launch's own).
+constexpr size_t kStatusWords = 48;
+inline unsigned* dt_count(unsigned* status, bool extrema) { return status + (extrema ? 32 : 16); }
+
+// One launch up to this many cells, two above: the arrivals at one count wait
+// their turn, and 64 workgroups of more cells each take longer than a second
+// launch.  Measured (us, one launch against two): 64^2 4.1, 5.6; 128^2 4.6, 5.6;
+// 181^2 4.9, 5.6; 256^2 5.7, 5.5; 512^2 10.3, 6.9.
+constexpr size_t kDtOneLaunch = 40000;
+constexpr int kDtArrivals = 64;
+inline int dt_arrivals(size_t n) {
+  const size_t want = (n + kDtThreads - 1) / kDtThreads;
+  return (int)(want < (size_t)kDtArrivals ? want : kDtArrivals);
+}
+
 struct DtParams {
   const double* __restrict__ Q;
   double* partial;   // [2][kDtBlocks] (context scratch holds [3][kDtBlocks])
+  unsigned* count;   // arrivals, zero between launches; null: the partials only
   double* dt;
   unsigned* status;
   int nx, ny;
@@ -50,6 +70,8 @@ __device__ __forceinline__ void dt_cell(const double* __restrict__ Q, size_t n, 
   }
 }
 
+// FINISH: the last workgroup writes dt.
+template <bool FINISH>
 __global__ __launch_bounds__(kDtThreads) void dt_reduce_kernel(DtParams P) {
 #pragma clang fp contract(off)
   __shared__ double red[kDtThreads / 64];
@@ -61,6 +83,13 @@ __global__ __launch_bounds__(kDtThreads) void dt_reduce_kernel(DtParams P) {
     dt_cell(P.Q, n, s, P.gamma, P.mu, P.dx, P.dy, conv, visc, bad);
   }
   if (bad) atomicOr(P.status, 1u);
+  if (FINISH) {
+    double v[2] = {conv, visc};
+    const double id[2] = {__builtin_inf(), __builtin_inf()};
+    dt_commit(v, id, P.partial, P.count, [](int, double x, double y) { return fmin(x, y); },
+              [&](const double* e) { dt_write(e[0], e[1], P.cfl, P.dt, P.status); });
+    return;
+  }
   conv = block_min(conv, red);
   visc = block_min(visc, red);
   if (threadIdx.x == 0) {
@@ -72,7 +101,6 @@ __global__ __launch_bounds__(kDtThreads) void dt_reduce_kernel(DtParams P) {
 __global__ __launch_bounds__(kDtThreads) void dt_finish_kernel(const double* partial, int nblk,
                                                                double* dt, double cfl,
                                                                unsigned* status) {
-#pragma clang fp contract(off)
   __shared__ double red[kDtThreads / 64];
   double conv = __builtin_inf(), visc = __builtin_inf();
   for (int k = threadIdx.x; k < nblk; k += blockDim.x) {
@@ -81,15 +109,10 @@ __global__ __launch_bounds__(kDtThreads) void dt_finish_kernel(const double* par
   }
   conv = block_min(conv, red);
   visc = block_min(visc, red);
-  if (threadIdx.x == 0) {
-    const double d = cfl * fmin(visc / kAlphaV, conv);
-    *dt = d;
-    if (!(d > 0.0) || !isfinite(d)) atomicOr(status, 2u);
-  }
+  if (threadIdx.x == 0) dt_write(conv, visc, cfl, dt, status);
 }
 
-// Second pass of the time step without a context: as dt_finish_kernel, with
-// the status word in the same scratch as the partials.  A bad state seen by
+// Second pass of the time step without a context, with the status word in the same scratch as the partials.  A bad state seen by
 // the first pass makes dt NaN (the caller has no context to ask), and the
 // word is cleared for the next call.
 __global__ __launch_bounds__(kDtThreads) void dt_finish_noalloc_kernel(const double* partial,
@@ -112,101 +135,41 @@ __global__ __launch_bounds__(kDtThreads) void dt_finish_noalloc_kernel(const dou
   }
 }
 
-// dt from the extrema the stage-3 kernel left per workgroup, in two passes
-// like the reduction above: pass 1 folds the slots [3][nslot] into
-// kDtBlocks partial extrema, pass 2 (one workgroup) finishes with the
-// arithmetic of dt_cell and dt_finish_kernel -- the minimum over cells of
-// fl(dx/(|u|+c)) is fl(dx/max(|u|+c)), and that of fl(fl(dx dx)/fl(mu/rho))
-// is fl(fl(dx dx)/fl(mu/min rho)), since fl(d/x) is monotone in x.
-__device__ __forceinline__ double block_max(double v, double* red) {
+// dt from the extrema the stage-3 kernel left per workgroup, in one launch of up
+// to 64 workgroups (1.5e5 slots of a 4096^2 grid: 9.9 us, as two launches took)
+// and with the arithmetic of dt_cell -- the minimum over cells of
+// fl(dx/(|u|+c)) is fl(dx/max(|u|+c)), and that of fl(fl(dx dx)/fl(mu/rho)) is
+// fl(fl(dx dx)/fl(mu/min rho)), since fl(d/x) is monotone in x.
+// THREE_D (inviscid): the third extremum is max(|w|+c), else min rho.
+struct DtExtremaParams {
+  const double* slots;   // [3][nslot]
+  int nslot;
+  double* partial;       // [3][kDtBlocks]
+  unsigned* count;
+  double* dt;
+  unsigned* status;
+  double cfl, dx, dy, dz, mu;
+};
+template <bool THREE_D>
+__global__ __launch_bounds__(kDtThreads) void dt_extrema_kernel(DtExtremaParams P) {
+  const double id[3] = {0.0, 0.0, THREE_D ? 0.0 : __builtin_inf()};
+  double v[3] = {id[0], id[1], id[2]};
+  auto fold = [](int m, double x, double y) {
+    return THREE_D || m < 2 ? fmax(x, y) : fmin(x, y);
+  };
+  for (int k = blockIdx.x * kDtThreads + threadIdx.x; k < P.nslot; k += gridDim.x * kDtThreads)
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-  const int w = threadIdx.x >> 6;
-  __syncthreads();
-  if (__lane_id() == 0) red[w] = v;
-  __syncthreads();
-  double r = red[0];
-  for (int k = 1; k < (int)(blockDim.x >> 6); ++k) r = fmax(r, red[k]);
-  return r;
-}
-
-// MAX3: the third extremum is a maximum (3D: max(|w|+c)), else a minimum
-// (2D: min rho).
-template <bool MAX3 = false>
-__global__ __launch_bounds__(kDtThreads) void dt_extrema_reduce_kernel(const double* slots,
-                                                                       int nslot,
-                                                                       double* partial) {
-  __shared__ double red[kDtThreads / 64];
-  double a = 0.0, b = 0.0, r = MAX3 ? 0.0 : __builtin_inf();
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nslot; k += gridDim.x * blockDim.x) {
-    a = fmax(a, slots[k]);
-    b = fmax(b, slots[nslot + k]);
-    r = MAX3 ? fmax(r, slots[2 * nslot + k]) : fmin(r, slots[2 * nslot + k]);
-  }
-  a = block_max(a, red);
-  b = block_max(b, red);
-  r = MAX3 ? block_max(r, red) : block_min(r, red);
-  if (threadIdx.x == 0) {
-    partial[blockIdx.x] = a;
-    partial[kDtBlocks + blockIdx.x] = b;
-    partial[2 * kDtBlocks + blockIdx.x] = r;
-  }
-}
-
-__global__ __launch_bounds__(kDtThreads) void dt_from_extrema_kernel(const double* partial,
-                                                                     int nblk, double* dt,
-                                                                     double cfl, double dx,
-                                                                     double dy, double mu,
-                                                                     unsigned* status) {
+    for (int m = 0; m < 3; ++m) v[m] = fold(m, v[m], P.slots[(size_t)m * P.nslot + k]);
+  dt_commit(v, id, P.partial, P.count, fold, [&](const double* e) {
 #pragma clang fp contract(off)
-  __shared__ double red[kDtThreads / 64];
-  double a = 0.0, b = 0.0, r = __builtin_inf();
-  for (int k = threadIdx.x; k < nblk; k += blockDim.x) {
-    a = fmax(a, partial[k]);
-    b = fmax(b, partial[kDtBlocks + k]);
-    r = fmin(r, partial[2 * kDtBlocks + k]);
-  }
-  a = block_max(a, red);
-  b = block_max(b, red);
-  r = block_min(r, red);
-  if (threadIdx.x == 0) {
-    const double conv = fmin(dx / a, dy / b);
-    double visc = __builtin_inf();
-    if (mu > 0.0) {
-      const double nu = mu / r;
-      visc = fmin(dx * dx / nu, dy * dy / nu);
+    double conv = fmin(P.dx / e[0], P.dy / e[1]), visc = __builtin_inf();
+    if (THREE_D) conv = fmin(P.dx / e[0], fmin(P.dy / e[1], P.dz / e[2]));
+    if (!THREE_D && P.mu > 0.0) {
+      const double nu = P.mu / e[2];
+      visc = fmin(P.dx * P.dx / nu, P.dy * P.dy / nu);
     }
-    const double d = cfl * fmin(visc / kAlphaV, conv);
-    *dt = d;
-    if (!(d > 0.0) || !isfinite(d)) atomicOr(status, 2u);
-  }
-}
-
-// 3D (inviscid): dt = cfl min(dx/a, dy/b, dz/c) from the partial maxima of
-// |u|+c, |v|+c, |w|+c, with the arithmetic of dt3_reduce_kernel and
-// dt_finish_kernel.
-__global__ __launch_bounds__(kDtThreads) void dt3_from_extrema_kernel(const double* partial,
-                                                                      int nblk, double* dt,
-                                                                      double cfl, double dx,
-                                                                      double dy, double dz,
-                                                                      unsigned* status) {
-#pragma clang fp contract(off)
-  __shared__ double red[kDtThreads / 64];
-  double a = 0.0, b = 0.0, c = 0.0;
-  for (int k = threadIdx.x; k < nblk; k += blockDim.x) {
-    a = fmax(a, partial[k]);
-    b = fmax(b, partial[kDtBlocks + k]);
-    c = fmax(c, partial[2 * kDtBlocks + k]);
-  }
-  a = block_max(a, red);
-  b = block_max(b, red);
-  c = block_max(c, red);
-  if (threadIdx.x == 0) {
-    const double conv = fmin(dx / a, fmin(dy / b, dz / c));
-    const double d = cfl * fmin(__builtin_inf() / kAlphaV, conv);
-    *dt = d;
-    if (!(d > 0.0) || !isfinite(d)) atomicOr(status, 2u);
-  }
+    dt_write(conv, visc, P.cfl, P.dt, P.status);
+  });
 }
 
 // Self-test of div_rb (the shared-reciprocal quotient of the time-step

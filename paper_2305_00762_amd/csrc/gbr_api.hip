@@ -34,7 +34,7 @@ struct gbr_ctx {
   double* d_time;             // device time of Q^n (moving boundary segments)
   int device;
   int export_flags;
-  unsigned* d_status;         // [4]
+  unsigned* d_status;         // [4] status, then dt_count (kStatusWords)
   double* d_partial;          // [3][kDtBlocks] time-step partial extrema
   double* d_dtx;              // [3][slots] per-wave time-step extrema of a stage-3 output
   int dtx_cap;                // slots d_dtx holds (the most of any tile shape)
@@ -136,7 +136,7 @@ int gbr_init(int nx, int ny, double gamma, double mu, double Pr, gbr_ctx** out) 
   c->recon = GBR_RECON_PRIM; c->mp_mode = GBR_MP_FLAGGED; c->order = 7;
   c->precision = GBR_PREC_FP64; c->detector = GBR_DET_PLAIN;
   if (hipGetDevice(&c->device) != hipSuccess) { delete c; return GBR_EDEVICE; }
-  if (hipMalloc(&c->d_status, 4 * sizeof(unsigned)) != hipSuccess) { delete c; return GBR_ENOMEM; }
+  if (hipMalloc(&c->d_status, kStatusWords * sizeof(unsigned)) != hipSuccess) { delete c; return GBR_ENOMEM; }
   if (hipMalloc(&c->d_partial, 3 * kDtBlocks * sizeof(double)) != hipSuccess) {
     (void)hipFree(c->d_status); delete c; return GBR_ENOMEM;
   }
@@ -160,7 +160,7 @@ int gbr_init(int nx, int ny, double gamma, double mu, double Pr, gbr_ctx** out) 
     (void)hipFree(c->d_time); delete c; return GBR_ENOMEM;
   }
   double* noalloc = nullptr;   // set-up of the allocation-free entry point on this device
-  if (hipMemset(c->d_status, 0, 4 * sizeof(unsigned)) != hipSuccess ||
+  if (hipMemset(c->d_status, 0, kStatusWords * sizeof(unsigned)) != hipSuccess ||
       hipMemset(c->d_time, 0, sizeof(double)) != hipSuccess ||
       noalloc_scratch(&noalloc) != GBR_OK || hipDeviceSynchronize() != hipSuccess) {
     (void)hipFree(c->d_status); (void)hipFree(c->d_partial); (void)hipFree(c->d_sides);
@@ -513,14 +513,20 @@ int gbr_compute_dt(gbr_ctx* c, const double* Q, double cfl, double* dt_dev, void
   if (!c || !Q || !dt_dev || !(cfl > 0.0)) return GBR_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   DtParams P{};
-  P.Q = Q; P.partial = c->d_partial; P.dt = dt_dev; P.status = c->d_status;
+  P.Q = Q; P.partial = c->d_partial; P.count = dt_count(c->d_status, false);
+  P.dt = dt_dev; P.status = c->d_status;
   P.nx = c->nx; P.ny = c->ny;
   P.dx = (c->x1 - c->x0) / c->nx; P.dy = (c->y1 - c->y0) / c->ny;
   P.gamma = c->gamma; P.mu = c->mu; P.cfl = cfl;
-  const int blocks = dt_blocks((size_t)c->nx * c->ny);
-  hipLaunchKernelGGL(dt_reduce_kernel, dim3(blocks), dim3(kDtThreads), 0, s, P);
-  hipLaunchKernelGGL(dt_finish_kernel, dim3(1), dim3(kDtThreads), 0, s, c->d_partial, blocks,
-                     dt_dev, cfl, c->d_status);
+  const size_t n = (size_t)c->nx * c->ny;
+  if (n <= kDtOneLaunch) {
+    hipLaunchKernelGGL(dt_reduce_kernel<true>, dim3(dt_arrivals(n)), dim3(kDtThreads), 0, s, P);
+  } else {
+    const int blocks = dt_blocks(n);
+    hipLaunchKernelGGL(dt_reduce_kernel<false>, dim3(blocks), dim3(kDtThreads), 0, s, P);
+    hipLaunchKernelGGL(dt_finish_kernel, dim3(1), dim3(kDtThreads), 0, s, c->d_partial, blocks,
+                       dt_dev, cfl, c->d_status);
+  }
   c->rp_armed = 0;   // a step begun from the state itself
   return hip_ok(hipGetLastError());
 }
@@ -540,7 +546,7 @@ int gbr_compute_dt_noalloc(int nx, int ny, double dx, double dy, double gamma, d
   P.Q = Q; P.partial = ptr; P.dt = dt_dev; P.status = status;
   P.nx = nx; P.ny = ny; P.dx = dx; P.dy = dy; P.gamma = gamma; P.mu = mu; P.cfl = cfl;
   const int blocks = dt_blocks((size_t)nx * ny);   // <= kDtBlocks: the partials fit
-  hipLaunchKernelGGL(dt_reduce_kernel, dim3(blocks), dim3(kDtThreads), 0, s, P);
+  hipLaunchKernelGGL(dt_reduce_kernel<false>, dim3(blocks), dim3(kDtThreads), 0, s, P);
   hipLaunchKernelGGL(dt_finish_noalloc_kernel, dim3(1), dim3(kDtThreads), 0, s,
                      (const double*)ptr, blocks, dt_dev, cfl, status);
   return hip_ok(hipGetLastError());
@@ -549,13 +555,13 @@ int gbr_compute_dt_noalloc(int nx, int ny, double dx, double dy, double gamma, d
 int gbr_stage_dt(gbr_ctx* c, double cfl, double* dt_dev, void* stream) {
   if (!c || !dt_dev || !(cfl > 0.0) || c->stage3_slots <= 0) return GBR_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  const int nslot = c->stage3_slots;
-  const int blocks = dt_blocks((size_t)nslot);
-  hipLaunchKernelGGL(dt_extrema_reduce_kernel<false>, dim3(blocks), dim3(kDtThreads), 0, s,
-                     (const double*)c->d_dtx, nslot, c->d_partial);
-  hipLaunchKernelGGL(dt_from_extrema_kernel, dim3(1), dim3(kDtThreads), 0, s,
-                     (const double*)c->d_partial, blocks, dt_dev, cfl,
-                     (c->x1 - c->x0) / c->nx, (c->y1 - c->y0) / c->ny, c->mu, c->d_status);
+  DtExtremaParams P{};
+  P.slots = c->d_dtx; P.nslot = c->stage3_slots;
+  P.partial = c->d_partial; P.count = dt_count(c->d_status, true);
+  P.dt = dt_dev; P.status = c->d_status; P.cfl = cfl; P.mu = c->mu;
+  P.dx = (c->x1 - c->x0) / c->nx; P.dy = (c->y1 - c->y0) / c->ny;
+  hipLaunchKernelGGL(dt_extrema_kernel<false>, dim3(dt_arrivals(P.nslot)), dim3(kDtThreads), 0,
+                     s, P);
   c->stage3_slots = 0;
   c->rp_armed = c->rp_valid;
   return hip_ok(hipGetLastError());
@@ -1148,8 +1154,8 @@ struct gbr3_ctx {
   int order;
   int device;
   int export_flags;
-  unsigned* d_status;         // [4]
-  double* d_partial;          // [2][kDtBlocks]
+  unsigned* d_status;         // [4] status, then dt_count (kStatusWords)
+  double* d_partial;          // [3][kDtBlocks]
   double* d_R;                // [5][nz][ny][nx] residual accumulator
   double* d_dtx;              // [3][slots] per-wave time-step extrema of a stage-3 output
   int stage3_slots;           // slots of the last stage-3 call; 0: none since gbr3_stage_dt
@@ -1172,11 +1178,11 @@ int gbr3_init(int nx, int ny, int nz, double gamma, gbr3_ctx** out) {
   const size_t n = (size_t)nx * ny * nz;
   const size_t zslots = (size_t)col3_tiles(nx, ny, nz) * kCol3Waves;
   bool ok = hipGetDevice(&c->device) == hipSuccess &&
-            hipMalloc(&c->d_status, 4 * sizeof(unsigned)) == hipSuccess &&
+            hipMalloc(&c->d_status, kStatusWords * sizeof(unsigned)) == hipSuccess &&
             hipMalloc(&c->d_partial, 3 * kDtBlocks * sizeof(double)) == hipSuccess &&
             hipMalloc(&c->d_R, 5 * n * sizeof(double)) == hipSuccess &&
             hipMalloc(&c->d_dtx, 3 * zslots * sizeof(double)) == hipSuccess &&
-            hipMemset(c->d_status, 0, 4 * sizeof(unsigned)) == hipSuccess &&
+            hipMemset(c->d_status, 0, kStatusWords * sizeof(unsigned)) == hipSuccess &&
             hipDeviceSynchronize() == hipSuccess;
   if (!ok) {
     (void)hipFree(c->d_status); (void)hipFree(c->d_partial); (void)hipFree(c->d_R);
@@ -1314,30 +1320,37 @@ int gbr3_compute_dt(gbr3_ctx* c, const double* Q, double cfl, double* dt_dev, vo
   if (!c || !Q || !dt_dev || !(cfl > 0.0)) return GBR_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   Dt3Params P{};
-  P.Q = Q; P.partial = c->d_partial; P.status = c->d_status;
+  P.Q = Q; P.partial = c->d_partial; P.count = dt_count(c->d_status, false);
+  P.dt = dt_dev; P.status = c->d_status; P.cfl = cfl;
   P.nx = c->n[0]; P.ny = c->n[1]; P.nz = c->n[2];
   P.dx = (c->hi[0] - c->lo[0]) / c->n[0];
   P.dy = (c->hi[1] - c->lo[1]) / c->n[1];
   P.dz = (c->hi[2] - c->lo[2]) / c->n[2];
   P.gamma = c->gamma;
-  const int blocks = dt_blocks((size_t)c->n[0] * c->n[1] * c->n[2]);
-  launch_dt3(P, blocks, s);
-  hipLaunchKernelGGL(dt_finish_kernel, dim3(1), dim3(kDtThreads), 0, s, c->d_partial, blocks,
-                     dt_dev, cfl, c->d_status);
+  const size_t n = (size_t)c->n[0] * c->n[1] * c->n[2];
+  if (n <= kDtOneLaunch) {
+    launch_dt3(P, dt_arrivals(n), true, s);
+  } else {
+    const int blocks = dt_blocks(n);
+    launch_dt3(P, blocks, false, s);
+    hipLaunchKernelGGL(dt_finish_kernel, dim3(1), dim3(kDtThreads), 0, s, c->d_partial, blocks,
+                       dt_dev, cfl, c->d_status);
+  }
   return hip_ok(hipGetLastError());
 }
 
 int gbr3_stage_dt(gbr3_ctx* c, double cfl, double* dt_dev, void* stream) {
   if (!c || !dt_dev || !(cfl > 0.0) || c->stage3_slots <= 0) return GBR_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  const int nslot = c->stage3_slots;
-  const int blocks = dt_blocks((size_t)nslot);
-  hipLaunchKernelGGL(dt_extrema_reduce_kernel<true>, dim3(blocks), dim3(kDtThreads), 0, s,
-                     (const double*)c->d_dtx, nslot, c->d_partial);
-  hipLaunchKernelGGL(dt3_from_extrema_kernel, dim3(1), dim3(kDtThreads), 0, s,
-                     (const double*)c->d_partial, blocks, dt_dev, cfl,
-                     (c->hi[0] - c->lo[0]) / c->n[0], (c->hi[1] - c->lo[1]) / c->n[1],
-                     (c->hi[2] - c->lo[2]) / c->n[2], c->d_status);
+  DtExtremaParams P{};
+  P.slots = c->d_dtx; P.nslot = c->stage3_slots;
+  P.partial = c->d_partial; P.count = dt_count(c->d_status, true);
+  P.dt = dt_dev; P.status = c->d_status; P.cfl = cfl;
+  P.dx = (c->hi[0] - c->lo[0]) / c->n[0];
+  P.dy = (c->hi[1] - c->lo[1]) / c->n[1];
+  P.dz = (c->hi[2] - c->lo[2]) / c->n[2];
+  hipLaunchKernelGGL(dt_extrema_kernel<true>, dim3(dt_arrivals(P.nslot)), dim3(kDtThreads), 0, s,
+                     P);
   c->stage3_slots = 0;
   return hip_ok(hipGetLastError());
 }

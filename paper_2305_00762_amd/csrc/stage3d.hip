@@ -49,8 +49,11 @@ int launch_stage3(Stage3Params P, int order, hipStream_t s) {
   return order == 4 ? launch<4>(P, s) : launch<7>(P, s);
 }
 
-void launch_dt3(const Dt3Params& P, int blocks, hipStream_t s) {
-  hipLaunchKernelGGL(dt3_reduce_kernel, dim3(blocks), dim3(kDtThreads), 0, s, P);
+void launch_dt3(const Dt3Params& P, int blocks, bool finish, hipStream_t s) {
+  if (finish)
+    hipLaunchKernelGGL(dt3_reduce_kernel<true>, dim3(blocks), dim3(kDtThreads), 0, s, P);
+  else
+    hipLaunchKernelGGL(dt3_reduce_kernel<false>, dim3(blocks), dim3(kDtThreads), 0, s, P);
 }
 
 }  // namespace gbr

@@ -486,7 +486,8 @@ __global__ __launch_bounds__(C::NT, C::MINW) void meg7_col3_kernel(Stage3Params 
 }
 
 // ---------------------------------------------------------------------------
-// Two-pass time step: pass 1 (pass 2 is dt_finish_kernel with no viscous limit).
+// Time step of a state (no viscous limit).
+template <bool FINISH>
 __global__ __launch_bounds__(kDtThreads) void dt3_reduce_kernel(Dt3Params P) {
 #pragma clang fp contract(off)
   __shared__ double red[kDtThreads / 64];
@@ -505,6 +506,13 @@ __global__ __launch_bounds__(kDtThreads) void dt3_reduce_kernel(Dt3Params P) {
     conv = fmin(conv, fmin(P.dx / (fabs(u) + c), fmin(P.dy / (fabs(v) + c), P.dz / (fabs(w) + c))));
   }
   if (bad) atomicOr(P.status, 1u);
+  if (FINISH) {
+    double e[1] = {conv};
+    const double id[1] = {__builtin_inf()};
+    dt_commit(e, id, P.partial, P.count, [](int, double x, double y) { return fmin(x, y); },
+              [&](const double* m) { dt_write(m[0], __builtin_inf(), P.cfl, P.dt, P.status); });
+    return;
+  }
   conv = block_min(conv, red);
   if (threadIdx.x == 0) {
     P.partial[blockIdx.x] = conv;

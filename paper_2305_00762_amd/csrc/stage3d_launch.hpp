@@ -16,6 +16,6 @@ inline long long col3_tiles(int nx, int ny, int nz) {
 // Both kernels of a residual or stage call (P.tiles_*, ntiles filled here);
 // returns the waves of the column launch (a time-step slot each in stage 3).
 int launch_stage3(Stage3Params P, int order, hipStream_t s);
-void launch_dt3(const Dt3Params& P, int blocks, hipStream_t s);
+void launch_dt3(const Dt3Params& P, int blocks, bool finish, hipStream_t s);
 
 }  // namespace gbr

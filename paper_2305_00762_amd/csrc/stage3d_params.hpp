@@ -26,14 +26,15 @@ struct Stage3Params {
   double* dtx;
 };
 
-// CFL time step in 3D (inviscid), Sec. 2.5: pass 1 of the two-pass
-// reduction (pass 2 is dt_finish_kernel with no viscous limit).
+// CFL time step in 3D (inviscid), Sec. 2.5.
 struct Dt3Params {
   const double* __restrict__ Q;
   double* partial;
+  unsigned* count;   // arrivals, zero between launches
+  double* dt;
   unsigned* status;
   int nx, ny, nz;
-  double dx, dy, dz, gamma;
+  double dx, dy, dz, gamma, cfl;
 };
 
 }  // namespace gbr
