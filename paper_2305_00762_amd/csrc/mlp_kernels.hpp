@@ -187,11 +187,14 @@ __device__ __forceinline__ void mlp_load_infer(const MlpImage& M, MlpInfer& F) {
   for (int nb = 0; nb < 2; ++nb) {
     const int n = 16 * nb + r;
     F.a1[nb] = *reinterpret_cast<const v8s*>(M.W1 + n * kMlpIn + 8 * g);
+    // the swapped columns two at a time (both halves start at an even column)
+    unsigned y[4];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int k = 8 * g + e;
-      F.a1y[nb][e] = (short)M.W1[n * kMlpIn + (k < kMlpF ? (k + kMlpF / 2) % kMlpF : k)];
+    for (int j = 0; j < 4; ++j) {
+      const int k = 8 * g + 2 * j, c = k < kMlpF / 2 ? k + kMlpF / 2 : k - kMlpF / 2;
+      y[j] = *reinterpret_cast<const unsigned*>(M.W1 + n * kMlpIn + (k < kMlpF ? c : k));
     }
+    F.a1y[nb] = __builtin_bit_cast(v8s, (uint4){y[0], y[1], y[2], y[3]});
     const v4s lo = *reinterpret_cast<const v4s*>(M.W2 + n * kMlpH + 4 * g);
     const v4s hi = *reinterpret_cast<const v4s*>(M.W2 + n * kMlpH + 16 + 4 * g);
     F.a2[nb] = (v8s){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
@@ -200,7 +203,7 @@ __device__ __forceinline__ void mlp_load_infer(const MlpImage& M, MlpInfer& F) {
       const int m = 16 * nb + 4 * g + i;
       F.b1[nb][i] = M.b[m];
       F.b2[nb][i] = M.b[kMlpH + m];
-      F.a3[4 * nb + i] = (short)f2bf(M.w3[m]);   // w3 is bf16-valued: exact
+      F.a3[4 * nb + i] = (short)(__float_as_uint(M.w3[m]) >> 16);   // w3 is bf16-valued
     }
   }
   F.b3 = M.b[2 * kMlpH];
@@ -402,6 +405,12 @@ __global__ __launch_bounds__(256) void mlp_features_kernel(MlpFeatParams P) {
 // evaluates exactly its own 64 cells, so the logit of lane l's cell lands in
 // lane l.  Evaluations below the margin are queued per wave and settled after
 // the last round; the flag bytes are then stored coalesced, one row per wave.
+// Bound by VALU and matrix issue and the latency of a block's start (four waves
+// per SIMD: 128 registers).  4096^2 Riemann field, 17% of the evaluations
+// settled plainly: 371 us; 350 with the settled cells' one address and stride,
+// 320 with the swapped weights loaded in pairs (the prologue of every wave).  A
+// workgroup that kept the weights for several blocks spilled (465 us); staging
+// rows by wave instead of 256 consecutive cells took 369.
 struct MlpChiParams {
   const double* Q;
   // optional: rho and p of Q already rounded to float32, [2][ny][nx] (the
@@ -540,14 +549,24 @@ __global__ __launch_bounds__(256, 4) void mlp_chi_kernel(MlpChiParams P) {
   }
   // plain labels of the queued evaluations, one per lane, from the FP64
   // density in memory
+  const bool inner = tx0 >= 2 && ty0 >= 2 && tx0 + kChiTX + 2 <= P.nx && ty0 + kChiTY + 2 <= P.ny;
   for (int k = l; k < nq; k += 64) {
     const int e = sQ[w][k], cell = e >> 1, ydir = e & 1;
     const int gi = ty0 + cell / kChiTX, gj = tx0 + cell % kChiTX;
-    const int si = ydir, sj = 1 - ydir;
-    auto rho = [&](int o) {
-      return P.Q[(size_t)gwrap(gi + o * si, P.ny, P.bcy) * P.nx + gwrap(gj + o * sj, P.nx, P.bcx)];
-    };
-    if (detector_flag(rho(-2), rho(-1), rho(0), rho(1), rho(2))) {
+    double r[5];
+    if (inner) {   // no ghost cells: one address and a stride
+      const double* q = P.Q + (size_t)gi * P.nx + gj;
+      const ptrdiff_t st = ydir ? P.nx : 1;
+#pragma unroll
+      for (int o = 0; o < 5; ++o) r[o] = q[(o - 2) * st];
+    } else {
+      const int si = ydir, sj = 1 - ydir;
+#pragma unroll
+      for (int o = 0; o < 5; ++o)
+        r[o] = P.Q[(size_t)gwrap(gi + (o - 2) * si, P.ny, P.bcy) * P.nx +
+                   gwrap(gj + (o - 2) * sj, P.nx, P.bcx)];
+    }
+    if (detector_flag(r[0], r[1], r[2], r[3], r[4])) {
       if (ydir) sCy[cell] = 2; else sCx[cell] = 1;
     }
   }
