@@ -95,14 +95,14 @@ def _path(prec, mlp, dtype, kernel, cons=False, order=7, mp_everywhere=False, pe
 PATHS = {
     # learned detector evaluated once per step on Q^n and reused by stages 2
     # and 3 (a change of the method; its L1 error is reported)
-    "fp32_mlp_step": _path("fp32", True, "f32+f64", "meg7_stage_kernel_f32<mlp>", per_step=True),
-    "fp32_mlp": _path("fp32", True, "f32+f64", "meg7_stage_kernel_f32<mlp>"),
-    "fp32": _path("fp32", False, "f32+f64", "meg7_stage_kernel_f32"),
-    "fp64": _path("fp64", False, "f64", "meg7_stage_kernel"),
+    "fp32_mlp_step": _path("fp32", True, "f32+f64", "meg7_line_kernel<f32,mlp>", per_step=True),
+    "fp32_mlp": _path("fp32", True, "f32+f64", "meg7_line_kernel<f32,mlp>"),
+    "fp32": _path("fp32", False, "f32+f64", "meg7_line_kernel<f32>"),
+    "fp64": _path("fp64", False, "f64", "meg7_line_kernel"),
     # MEG7-cons (Table 2): GRB and the MP procedure on conservative variables
-    "fp64_cons": _path("fp64", False, "f64", "meg7_stage_kernel<cons>", cons=True),
+    "fp64_cons": _path("fp64", False, "f64", "meg7_line_kernel<cons>", cons=True),
     # the fourth-order GRB subset (alpha = 4, beta = 0; eq. fourth)
-    "fp64_g4": _path("fp64", False, "f64", "meg7_stage_kernel<g4>", order=4),
+    "fp64_g4": _path("fp64", False, "f64", "meg7_line_kernel<g4>", order=4),
     # the MEG7 states at every interface (the MP test everywhere)
     "fp64_mpe": _path("fp64", False, "f64", "meg7_stage_kernel<mpe>", mp_everywhere=True),
 }
@@ -202,23 +202,25 @@ def cpu_model():
     return info
 
 
-def load_valu(kernel_prefix, workload):
+def load_valu(kernel, workload):
     """VALU wave-instructions per launch of a stage kernel from the committed
-    rocprofv3 SQ-counter summary, if any (its SQ_INSTS_VALU line)."""
-    path = os.path.join(ROOT, "profiles", f"meg7_stage_kernels_{workload}_sq_counters.txt")
+    rocprofv3 SQ-counter summary, if any (its SQ_INSTS_VALU line), taken on the
+    current kernel sources (its 'source_sha = <hash>' line)."""
+    path = os.path.join(ROOT, "profiles", f"meg7_line_kernels_{workload}_sq_counters.txt")
     if not os.path.exists(path):
         return None
+    instr, sha = None, None
     for line in open(path):
         f = line.split()
-        if len(f) >= 4 and f[0] == kernel_prefix and f[1] == "SQ_INSTS_VALU" and f[2] == "mean":
-            return float(f[3])
-    return None
+        if len(f) >= 4 and f[0] == kernel and f[1] == "SQ_INSTS_VALU" and f[2] == "mean":
+            instr = float(f[3])
+        elif len(f) == 3 and f[0] == "source_sha":
+            sha = f[2]
+    return instr if sha == kernel_source_sha() else None
 
 
 def valu_roofline(kernel, workload, avg_us):
-    prefix = {"meg7_stage_kernel_f32<mlp>": "meg7_stage_kernel_f32",
-              "meg7_stage_kernel": "meg7_stage_kernel<"}.get(kernel)
-    instr = load_valu(prefix, workload) if prefix else None
+    instr = load_valu(kernel, workload)
     if instr is None:
         return None
     achieved = instr * 64 / (avg_us * 1e-6)
@@ -869,7 +871,7 @@ def bench_2d(a, workload, steps_arg, stream, cpu=True, secondary=False):
     # the timed launches over their summed duration from the library's events
     alg_bytes = sum(BYTES_PER_CELL_STAGE.values()) * cells * steps
     achieved = alg_bytes / (stage_ms * 1e-3) / 1e9
-    kname = head.kernel.replace("<", "_").replace(">", "")
+    kname = head.kernel.replace("<", "_").replace(",", "_").replace(">", "")
     out = {
         "value": head_rec["value"],
         "ms_per_step": head_rec["ms_per_step"],

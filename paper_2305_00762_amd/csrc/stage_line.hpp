@@ -23,13 +23,14 @@
 // central one in float32.  The mean flux, MP limiter, viscous flux and
 // divergence are FP64.
 //
-// What bounds it: VALU issue, busy 81% at 4096^2 (15x15 tiles, K = 4).  The
-// barrier-phased form with per-line buffers before it issued 1.14 times the
-// VALU and 2.8 times the LDS instructions, whose waits held it at 57%.  The 48
-// running sums of K = 4 fit 168 registers, 3 waves per SIMD; K = 8 does not.
+// What bounds it: VALU issue, busy 83% at 4096^2 (15x15 tiles, K = 4; 86% on
+// 31x15, FP32 94 and 95%).  The barrier-phased form with per-line buffers before
+// it issued 1.2 times the VALU and 2.8 times the LDS instructions, whose waits
+// held it at 57%.  The 48 running sums of K = 4 fit 168 registers, 3 waves per
+// SIMD; K = 8 does not.
 // Measured per stage (Riemann field, that form -> this): 4096^2 FP64 1071 ->
-// 703 us (15x15), 676 (31x15), FP32 803 -> 622; 1024^2 FP64 91 -> 60; viscous
-// shear 2048^2 FP64 303 -> 195, FP32 235 -> 185.  Unphysical smooth states go
+// 678 us (15x15), 663 (31x15), FP32 803 -> 619; 1024^2 FP64 91 -> 57; viscous
+// shear 2048^2 FP64 303 -> 192, FP32 235 -> 177.  Unphysical smooth states go
 // through the same per-wave queue as flagged interfaces (kFirstOrder): their
 // first-order fallback inline held registers and split every interface in
 // blocks; a step of the 1280x640 MEG7-cons tube took 212 us with it, 193
