@@ -26,12 +26,6 @@ inline int dt_blocks(size_t n) {
   return (int)(want < cap ? want : cap);
 }
 
-// A context's status words, then the arrival counts: one for the step of a state
-// and one for that of stage-3 extrema (their launches differ in size, and a
-// count is its launch's own).
-constexpr size_t kStatusWords = 48;
-inline unsigned* dt_count(unsigned* status, bool extrema) { return status + (extrema ? 32 : 16); }
-
 // One launch up to this many cells, two above: the arrivals at one count wait
 // their turn, and 64 workgroups of more cells each take longer than a second
 // launch.  Measured (us, one launch against two): 64^2 4.1, 5.6; 128^2 4.6, 5.6;
@@ -41,6 +35,22 @@ constexpr int kDtArrivals = 64;
 inline int dt_arrivals(size_t n) {
   const size_t want = (n + kDtThreads - 1) / kDtThreads;
   return (int)(want < (size_t)kDtArrivals ? want : kDtArrivals);
+}
+
+// Scratch of the one-launch forms, in turn: kDtTurns sets for the step of a
+// state and as many for that of stage-3 extrema, so that calls of one context
+// that overlap on several streams do not meet in a count.  A set is kDtArrivals
+// slots of each row of the partial extrema and a word behind the status words.
+constexpr unsigned kDtTurns = 8;
+constexpr size_t kStatusWords = 16 + 2 * kDtTurns;
+static_assert(2 * kDtTurns * kDtArrivals <= (unsigned)kDtBlocks, "sets fit the partials");
+struct DtSet {
+  double* partial;
+  unsigned* count;
+};
+inline DtSet dt_set(double* partial, unsigned* status, unsigned& turn, bool extrema) {
+  const unsigned k = (turn++ % kDtTurns) + (extrema ? kDtTurns : 0);
+  return {partial + k * kDtArrivals, status + 16 + k};
 }
 
 struct DtParams {

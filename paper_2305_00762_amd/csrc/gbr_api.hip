@@ -34,7 +34,8 @@ struct gbr_ctx {
   double* d_time;             // device time of Q^n (moving boundary segments)
   int device;
   int export_flags;
-  unsigned* d_status;         // [4] status, then dt_count (kStatusWords)
+  unsigned* d_status;         // [4] status, then the arrival counts (kStatusWords)
+  unsigned dt_turn = 0;       // next set of the one-launch time step
   double* d_partial;          // [3][kDtBlocks] time-step partial extrema
   double* d_dtx;              // [3][slots] per-wave time-step extrema of a stage-3 output
   int dtx_cap;                // slots d_dtx holds (the most of any tile shape)
@@ -517,13 +518,15 @@ int gbr_compute_dt(gbr_ctx* c, const double* Q, double cfl, double* dt_dev, void
   if (!c || !Q || !dt_dev || !(cfl > 0.0)) return GBR_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   DtParams P{};
-  P.Q = Q; P.partial = c->d_partial; P.count = dt_count(c->d_status, false);
+  P.Q = Q; P.partial = c->d_partial;
   P.dt = dt_dev; P.status = c->d_status;
   P.nx = c->nx; P.ny = c->ny;
   P.dx = (c->x1 - c->x0) / c->nx; P.dy = (c->y1 - c->y0) / c->ny;
   P.gamma = c->gamma; P.mu = c->mu; P.cfl = cfl;
   const size_t n = (size_t)c->nx * c->ny;
   if (n <= kDtOneLaunch) {
+    const DtSet set = dt_set(c->d_partial, c->d_status, c->dt_turn, false);
+    P.partial = set.partial; P.count = set.count;
     hipLaunchKernelGGL(dt_reduce_kernel<true>, dim3(dt_arrivals(n)), dim3(kDtThreads), 0, s, P);
   } else {
     const int blocks = dt_blocks(n);
@@ -561,7 +564,8 @@ int gbr_stage_dt(gbr_ctx* c, double cfl, double* dt_dev, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   DtExtremaParams P{};
   P.slots = c->d_dtx; P.nslot = c->stage3_slots;
-  P.partial = c->d_partial; P.count = dt_count(c->d_status, true);
+  const DtSet set = dt_set(c->d_partial, c->d_status, c->dt_turn, true);
+  P.partial = set.partial; P.count = set.count;
   P.dt = dt_dev; P.status = c->d_status; P.cfl = cfl; P.mu = c->mu;
   P.dx = (c->x1 - c->x0) / c->nx; P.dy = (c->y1 - c->y0) / c->ny;
   hipLaunchKernelGGL(dt_extrema_kernel<false>, dim3(dt_arrivals(P.nslot)), dim3(kDtThreads), 0,
@@ -1158,7 +1162,8 @@ struct gbr3_ctx {
   int order;
   int device;
   int export_flags;
-  unsigned* d_status;         // [4] status, then dt_count (kStatusWords)
+  unsigned* d_status;         // [4] status, then the arrival counts (kStatusWords)
+  unsigned dt_turn = 0;       // next set of the one-launch time step
   double* d_partial;          // [3][kDtBlocks]
   double* d_R;                // [5][nz][ny][nx] residual accumulator
   double* d_dtx;              // [3][slots] per-wave time-step extrema of a stage-3 output
@@ -1324,7 +1329,7 @@ int gbr3_compute_dt(gbr3_ctx* c, const double* Q, double cfl, double* dt_dev, vo
   if (!c || !Q || !dt_dev || !(cfl > 0.0)) return GBR_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   Dt3Params P{};
-  P.Q = Q; P.partial = c->d_partial; P.count = dt_count(c->d_status, false);
+  P.Q = Q; P.partial = c->d_partial;
   P.dt = dt_dev; P.status = c->d_status; P.cfl = cfl;
   P.nx = c->n[0]; P.ny = c->n[1]; P.nz = c->n[2];
   P.dx = (c->hi[0] - c->lo[0]) / c->n[0];
@@ -1333,6 +1338,8 @@ int gbr3_compute_dt(gbr3_ctx* c, const double* Q, double cfl, double* dt_dev, vo
   P.gamma = c->gamma;
   const size_t n = (size_t)c->n[0] * c->n[1] * c->n[2];
   if (n <= kDtOneLaunch) {
+    const DtSet set = dt_set(c->d_partial, c->d_status, c->dt_turn, false);
+    P.partial = set.partial; P.count = set.count;
     launch_dt3(P, dt_arrivals(n), true, s);
   } else {
     const int blocks = dt_blocks(n);
@@ -1348,7 +1355,8 @@ int gbr3_stage_dt(gbr3_ctx* c, double cfl, double* dt_dev, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   DtExtremaParams P{};
   P.slots = c->d_dtx; P.nslot = c->stage3_slots;
-  P.partial = c->d_partial; P.count = dt_count(c->d_status, true);
+  const DtSet set = dt_set(c->d_partial, c->d_status, c->dt_turn, true);
+  P.partial = set.partial; P.count = set.count;
   P.dt = dt_dev; P.status = c->d_status; P.cfl = cfl;
   P.dx = (c->hi[0] - c->lo[0]) / c->n[0];
   P.dy = (c->hi[1] - c->lo[1]) / c->n[1];
