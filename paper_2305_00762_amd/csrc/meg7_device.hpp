@@ -94,22 +94,10 @@ __device__ __forceinline__ double grad6(double pm3, double pm2, double pm1, doub
   return (45.0 * (p1 - pm1) - 9.0 * (p2 - pm2) + (p3 - pm3)) * (1.0 / 60.0);
 }
 
-// Density detector psi of Sec. 2.4 with eps in numerator and denominator.
-// Evaluated with one rounding per operation in a fixed order (no FMA
-// contraction) and an IEEE division, so that the decision psi < psi_c is
-// reproducible bit for bit.
-__device__ __forceinline__ double detector_psi(double rm2, double rm1, double r0,
-                                                         double rp1, double rp2) {
-#pragma clang fp contract(off)
-  double a = fabs(r0 - rm1) + fabs((r0 - 2.0 * rm1) + rm2);
-  double b = fabs(r0 - rp1) + fabs((r0 - 2.0 * rp1) + rp2);
-  double num = (2.0 * a) * b + kDetEps;
-  double den = (a * a + b * b) + kDetEps;
-  return num / den;
-}
-
-// The detector's decision psi < psi_c (= 1/2) without the division: with
-// num = 2ab + eps and den = a^2 + b^2 + eps as above (both positive),
+// Density detector of Sec. 2.4, eps in numerator and denominator: the decision
+// psi < psi_c (= 1/2) of psi = fl(num / den), num = 2ab + eps, den = a^2 + b^2 +
+// eps (both positive), every operation rounded on its own in a fixed order so
+// that it is reproducible bit for bit, but without the division:
 // fl(num / den) < 1/2 holds exactly when num / den < 1/2 - 2^-55 (the rounding
 // boundary below 1/2; a tie rounds to 1/2, whose significand is even), i.e.
 // when den - 2 num > den 2^-54.  That is 2 num < den: let 2^e <= 2 num < 2^(e+1)
@@ -493,23 +481,6 @@ __device__ __forceinline__ void conv_flux(const double W[4], double g1inv, doubl
   F[1] = m * W[1] + W[3];
   F[2] = m * W[2];
   F[3] = W[1] * (E + W[3]);
-}
-
-// Jump of the normal convective flux between states Wm and Wp, F(Wp) - F(Wm),
-// written on the primitive jumps so that it is exactly zero for equal states
-// and carries no cancellation of the flux magnitudes.
-__device__ __forceinline__ void conv_flux_jump(const double Wm[4], const double Wp[4],
-                                               double g1inv, double dF[4]) {
-  const double dr = Wp[0] - Wm[0], du = Wp[1] - Wm[1], dv = Wp[2] - Wm[2], dp = Wp[3] - Wm[3];
-  const double mp = Wp[0] * Wp[1];
-  const double dm = Wp[0] * du + Wm[1] * dr;  // jump of rho un
-  const double Em = Wm[3] * g1inv + 0.5 * Wm[0] * (Wm[1] * Wm[1] + Wm[2] * Wm[2]);
-  const double dE = dp * g1inv + 0.5 * (dr * (Wm[1] * Wm[1] + Wm[2] * Wm[2]) +
-                                        Wp[0] * (du * (Wp[1] + Wm[1]) + dv * (Wp[2] + Wm[2])));
-  dF[0] = dm;
-  dF[1] = mp * du + Wm[1] * dm + dp;
-  dF[2] = mp * dv + Wm[2] * dm;
-  dF[3] = Wp[1] * (dE + dp) + (Em + Wm[3]) * du;
 }
 
 // sin(x) for x in [0, pi/2]: its Taylor series to x^21 (truncation below
