@@ -231,7 +231,8 @@ int gbr_get_flags(gbr_ctx *ctx, uint8_t *sig_x, uint8_t *sig_y, void *stream);
 int gbr_timing(gbr_ctx *ctx, int enable);
 int gbr_timing_read(gbr_ctx *ctx, double *detector_ms, double *stage_ms, uint64_t *launches);
 
-/* Tile shapes of the stage kernel (31x15, 15x15, 63x7, 30x15, 15x7).
+/* Tile shapes of the stage kernel (31x15, 15x15, 63x7, 30x15; small grids take
+ * the 15x15 shape as 15x7 workgroups).
  * gbr_tiling_count() is the number of compiled shapes; gbr_set_tiling selects one (0 = default 31x15 cells per
  * workgroup); gbr_get_tiling reports the shape in use (the viscous form falls
  * back to variant 0 where a shape has no viscous build).  gbr_autotune times

@@ -156,6 +156,11 @@ int gbr_init(int nx, int ny, double gamma, double mu, double Pr, gbr_ctx** out) 
                   ((ny + tile_variants()[v].ty - 1) / tile_variants()[v].ty) * kMaxStageWaves;
     c->dtx_cap = t > c->dtx_cap ? t : c->dtx_cap;
   }
+  const int tx = tile_variants()[TILE_15x15].tx, cols = (nx + tx - 1) / tx;
+  if (cols * ((ny + tx - 1) / tx) < kTinyTiles15) {
+    const int t = cols * ((ny + kTinyTY - 1) / kTinyTY) * kTinyWaves;
+    c->dtx_cap = t > c->dtx_cap ? t : c->dtx_cap;
+  }
   if (hipMalloc(&c->d_dtx, 3 * (size_t)c->dtx_cap * sizeof(double)) != hipSuccess) {
     (void)hipFree(c->d_status); (void)hipFree(c->d_partial); (void)hipFree(c->d_sides);
     (void)hipFree(c->d_time); delete c; return GBR_ENOMEM;
@@ -405,10 +410,10 @@ static int launch_stage(gbr_ctx* c, int mode, const double* dt, const double* Qn
   P.tiles_x = (c->nx + v->tx - 1) / v->tx;
   P.ntiles = P.tiles_x * ((c->ny + v->ty - 1) / v->ty);
   if (tev && hipEventRecord(tev[1], s) != hipSuccess) return GBR_EDEVICE;
-  const int waves = variant_fn(c, vi)(P, s);
+  const int slots = variant_fn(c, vi)(P, s);
   if (tev && hipEventRecord(tev[2], s) != hipSuccess) return GBR_EDEVICE;
   if (mode == MODE_STAGE3) {
-    c->stage3_slots = P.ntiles * waves;
+    c->stage3_slots = slots;
     c->rp_valid = P.rp != nullptr;
     c->rp_src = out;
     c->rp_armed = 0;
@@ -476,10 +481,6 @@ int gbr_autotune(gbr_ctx* c, const double* Q, int reps, void* stream) {
   float best_ms = 1e30f;
   for (int v = 0; v < kNumVariants && rc == GBR_OK; ++v) {
     if (!variant_fn(c, v)) continue;
-    // the smallest tile leads on small grids alone (64^2 9.4 us against 12.2 of
-    // 15x15; 256^2 16.4 against 15.9, 600^2 37.4 against 36.1), and timing it on
-    // a large grid costs more than any other
-    if (v == TILE_15x7 && (long long)c->nx * c->ny > 512 * 512) continue;
     c->tiling = v;
     rc = launch_stage(c, MODE_RESIDUAL, nullptr, Q, Q, tmp, s);  // warm-up
     if (rc != GBR_OK) break;

@@ -5,14 +5,15 @@
 
 namespace gbr {
 
-// TX x TY tiles, K interfaces per lane.
+// TX x TY tiles, K interfaces per lane; returns the launch's time-step slots (a
+// wave each).
 template <class C, bool MLP, bool CONS, int ORD, bool LM, bool F32>
 int launch_line_cfg(const StageParams& P, hipStream_t s) {
   static_assert(C::LDS_BYTES <= 160 * 1024, "LDS per workgroup");
   static_assert(C::NT / 64 <= kMaxStageWaves, "time-step slots");
   hipLaunchKernelGGL((meg7_line_kernel<C, MLP, CONS, ORD, LM, F32>), dim3(P.ntiles), dim3(C::NT), 0,
                      s, P);
-  return C::NT / 64;
+  return P.ntiles * (C::NT / 64);
 }
 
 // Interfaces per lane by the number of tiles.  K = 4 reads and forms each cell
@@ -34,9 +35,21 @@ int launch_line_cfg(const StageParams& P, hipStream_t s) {
 // MEG7-cons needs more registers than four waves per SIMD leave, so its K = 1
 // ends earlier (K = 1, 2; 15x15): 128^2 16.4 19.1, 256^2 21.8 23.7 (324 tiles),
 // 400^2 35.2 28.9.
+// Below 100 tiles of 15x15 (MEG7-prim) the chip is nearly empty and 15x7 tiles of
+// one interface a lane, twice the workgroups, serve the shape: 24^2 to 128^2
+// Riemann 10.9 us a stage (events) against 13.2, viscous 9.4 against 10.8; at
+// 180^2 (144 tiles) 13.7 and 13.5, 11.2 and 10.9.
 constexpr int kFewTiles15 = 800, kFewTilesCons = 400, kMidTiles15 = 1900, kFewTiles31 = 448;
 template <bool VISC, bool MLP, bool F32 = false, bool CONS = false, int ORD = 7, bool LM = false>
 int launch_line15(const StageParams& P, hipStream_t s) {
+  if constexpr (!CONS && ORD == 7 && !LM)
+    if (P.ntiles < kTinyTiles15) {
+      using C = LineCfg<15, kTinyTY, 1, VISC, 4>;
+      StageParams T = P;
+      T.ntiles = P.tiles_x * ((P.ny + C::TY - 1) / C::TY);
+      static_assert(C::NT / 64 == kTinyWaves, "time-step slots");
+      return launch_line_cfg<C, MLP, CONS, ORD, LM, F32>(T, s);
+    }
   if constexpr (!VISC)
     if (P.ntiles < (CONS ? kFewTilesCons : kFewTiles15))
       return launch_line_cfg<LineCfg<15, 15, 1, VISC, CONS ? 3 : 4>, MLP, CONS, ORD, LM, F32>(P, s);
@@ -66,10 +79,6 @@ void fill_prim(TileVariant* v) {
   put(TILE_15x15, launch_line15<false, MLP, F32>, launch_line15<true, MLP, F32>);
   put(TILE_63x7, launch_line<63, 7, 4, 3, false, MLP, F32>, nullptr);
   put(TILE_30x15, launch_line<30, 15, 4, 3, false, MLP, F32>, nullptr);
-  // small grids: one interface per lane, twice the workgroups of 15x15 (64^2
-  // Riemann stage 9.4 us against 12.2, 256^2 13.2 against 15.8)
-  put(TILE_15x7, launch_line<15, 7, 1, 4, false, MLP, F32>,
-      launch_line<15, 7, 1, 4, true, MLP, F32>);
 }
 
 // The two larger shapes' launchers of another scheme: out[tile][viscous].

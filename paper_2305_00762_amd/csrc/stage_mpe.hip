@@ -7,7 +7,7 @@ int launch_mpe(const StageParams& P, hipStream_t s) {
   static_assert(C::LDS_BYTES <= 160 * 1024, "LDS per workgroup");
   static_assert(C::NT / 64 <= kMaxStageWaves, "time-step slots");
   hipLaunchKernelGGL((meg7_stage_kernel<C, CONS>), dim3(P.ntiles), dim3(C::NT), 0, s, P);
-  return C::NT / 64;
+  return P.ntiles * (C::NT / 64);
 }
 
 template <bool CONS>
@@ -24,7 +24,7 @@ void fill_mpe(TileVariant* v) {
 
 const TileVariant* tile_variants() {
   static const struct Table {
-    TileVariant v[kNumVariants] = {{31, 15}, {15, 15}, {63, 7}, {30, 15}, {15, 7}};
+    TileVariant v[kNumVariants] = {{31, 15}, {15, 15}, {63, 7}, {30, 15}};
     Table() {
       fill_fp64(v);
       fill_fp64_mlp(v);

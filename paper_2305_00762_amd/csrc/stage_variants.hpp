@@ -7,8 +7,8 @@
 
 namespace gbr {
 
-// A stage launcher enqueues one launch and returns its waves per workgroup: a
-// stage-3 launch leaves one time-step slot per wave.
+// A stage launcher enqueues one launch and returns its waves: a time-step slot
+// each in stage 3.
 using LaunchFn = int (*)(const StageParams&, hipStream_t);
 constexpr int kMaxStageWaves = 8;
 
@@ -23,7 +23,9 @@ struct TileVariant {
   LaunchFn ss[2][2];      // shock-stable HLLC, seventh order, FP64, plain: [cons][viscous]
   LaunchFn mpe[2][2];     // MP test at every interface, seventh order, FP64, plain: [cons][viscous]
 };
-enum : int { TILE_31x15 = 0, TILE_15x15, TILE_63x7, TILE_30x15, TILE_15x7, kNumVariants };
+enum : int { TILE_31x15 = 0, TILE_15x15, TILE_63x7, TILE_30x15, kNumVariants };
+// 15x15 grids of fewer tiles run 15x7 tiles of kTinyWaves waves (stage_launch.hpp).
+constexpr int kTinyTiles15 = 100, kTinyTY = 7, kTinyWaves = 4;
 const TileVariant* tile_variants();
 
 // The units' shares of the table.

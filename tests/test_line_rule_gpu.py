@@ -1,5 +1,5 @@
-"""Both sides of each line of the rule that gives a lane of a 15x15 tile one,
-two or four interfaces, on ragged grids, for every scheme that follows it.
+"""Both sides of each line of the rule that serves the 15x15 shape by 15x7 tiles
+or gives a lane one, two or four interfaces, on ragged grids, for every scheme that follows it.
 
 Bars: as in the other residual tests (flags bit for bit, 1e-12 in FP64, 1e-6 in
 FP32 bulk)."""
@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("scheme", sorted(SCHEMES))
-@pytest.mark.parametrize("tx,ty", [(20, 19), (20, 21),      # 380, 420 tiles
+@pytest.mark.parametrize("tx,ty", [(9, 11), (10, 10),       # 99, 100 tiles
+                                   (20, 19), (20, 21),      # 380, 420
                                    (28, 28), (29, 28),      # 784, 812
                                    (43, 44), (44, 44)])     # 1892, 1936
 def test_interfaces_per_lane(tx, ty, scheme):

@@ -12,7 +12,7 @@ from paper_2305_00762_amd import gbr
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("tiling", range(5))
+@pytest.mark.parametrize("tiling", range(4))
 @pytest.mark.parametrize("mu", [0.0, 1e-3])
 def test_every_remainder(tiling, mu):
     require_gpu()
