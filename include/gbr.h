@@ -103,7 +103,8 @@ int gbr_set_geometry(gbr_ctx *ctx, double x0, double x1, double y0, double y1,
  * the 31x15 and 15x15 tilings), precision = GBR_PREC_FP64
  * or GBR_PREC_FP32_BULK (GRB reconstruction and Riemann solver in float32 on
  * local jumps, with FP64 state, mean fluxes, stage update and flux
- * differencing), detector = GBR_DET_PLAIN
+ * differencing; for states whose density, pressure and fluxes, up to rho c^3,
+ * are normal float32 numbers), detector = GBR_DET_PLAIN
  * (density detector, Sec. 2.4) or GBR_DET_MLP (learned detector, needs
  * gbr_mlp_set_weights).  Unsupported combinations return GBR_EUNSUPPORTED
  * and leave the scheme unchanged. */

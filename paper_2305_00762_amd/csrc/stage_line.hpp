@@ -54,14 +54,15 @@ __device__ __forceinline__ void hllc_diss_f32(const float WL[4], const float WR[
   const float rl = WL[0], ul = WL[1], vl = WL[2], pl = WL[3];
   const float rr = WR[0], ur = WR[1], vr = WR[2], pr = WR[3];
   const float dr = dW[0], du = dW[1], dv = dW[2], dp = dW[3];
-  // 1/sqrt(rho_L rho_R) gives both specific volumes and the Roe weights; the
-  // Roe sound speed from the jumps, as in hllc_n
-  const float y = rsqf(rl * rr), y2 = y * y;
+  // 1/sqrt(rho) of each side gives the specific volumes and the Roe weights (an
+  // estimate each: the product of the densities leaves float32's range above
+  // 1.8e19 and below 1e-19); the Roe sound speed from the jumps, as in hllc_n
+  const float yl = rsqf(rl), yr = rsqf(rr);
   const float kl2 = ul * ul + vl * vl, kr2 = ur * ur + vr * vr;
   const float El = pl * g1inv + 0.5f * rl * kl2;
   const float Er = pr * g1inv + 0.5f * rr * kr2;
-  const float al = gamma * pl * (rr * y2), ar = gamma * pr * (rl * y2);
-  const float t = rr * y;
+  const float al = gamma * pl * (yl * yl), ar = gamma * pr * (yr * yr);
+  const float t = rr * yr * yl;
   const float wl = rcpf(1.0f + t), wr = t * wl;
   const float ut = wl * ul + wr * ur;
   const float at = wl * al + wr * ar +
