@@ -5,12 +5,16 @@ The Euler equations scale: rho and p by s leave the velocities and multiply
 every flux by s; p by s alone multiplies the velocities by sqrt(s).  So the bars
 are those of the unscaled fields: flags bit for bit and a residual within 1e-12
 (FP64) or 1e-6 (FP32 bulk) of the flux-divergence scale.  FP32 bulk: the scales
-at which the fluxes themselves, rho c^3 among them, are normal float32 numbers."""
+at which the fluxes themselves, rho c^3 among them, are normal float32 numbers.
+FP64: up to 1e150, where the detector's squared density jumps are finite."""
 import pytest
 
+import oracle as O
 from paper_2305_00762_amd import gbr
 from paper_2305_00762_amd import problems as PB
-from test_line_forms_gpu import check, noise
+from gpu_util import gpu_residual, ocfg, res_err
+from test_3d_gpu import check3
+from test_line_forms_gpu import SCHEMES, check, noise
 
 pytestmark = pytest.mark.gpu
 
@@ -34,3 +38,32 @@ def test_fp32_bulk(kind, rho, p):
     for tiling in (0, 1):
         check(f"fp32 {kind} rho {rho:g} p {p:g} t{tiling}", P, tiling,
               precision=gbr.GBR_PREC_FP32_BULK)
+
+
+SCALES = [(1e-120, 1e-120), (1e120, 1e120), (1.0, 1e130), (1.0, 1e-130), (1e40, 1e180),
+          (1e-40, 1e-180)]
+FAR = [(1e-150, 1e-150), (1e150, 1e150), (1e-250, 1e-250)]
+
+
+@pytest.mark.parametrize("kind", ["vortex", "noise"])
+@pytest.mark.parametrize("scheme,rho,p", [
+    (s, *x) for s in ("prim", "cons", "order4", "ss", "mpe")
+    for x in SCALES + (FAR if s != "cons" else [])])   # (MEG7-cons multiplies two densities)
+def test_fp64(scheme, rho, p, kind):
+    P = scaled(kind, 50, 37, rho, p)
+    if scheme != "mpe":
+        return check(f"fp64 {scheme} {kind} rho {rho:g} p {p:g}", P, 0, **SCHEMES[scheme])
+    R, sx, sy, st = gpu_residual(P, mp_mode=1)
+    Ro, ox, oy, _ = O.residual(ocfg(P, mp_mode=1), P.Q, want_flags=True)
+    assert st == gbr.GBR_OK and (sx == ox).all() and (sy == oy).all()
+    assert (res_err(R, Ro, P) <= 1e-12).all()
+
+
+@pytest.mark.parametrize("rho,p", SCALES + FAR)
+def test_3d(rho, p):
+    P = PB.riemann3d(26, seed=2, ny=17, nz=21)
+    r, s = P.Q[0], (p / rho) ** 0.5
+    u, v, w = P.Q[1] / r, P.Q[2] / r, P.Q[3] / r
+    pr = (P.gamma - 1) * (P.Q[4] - 0.5 * r * (u * u + v * v + w * w))
+    P.Q = PB.prim_to_state3(r * rho, u * s, v * s, w * s, pr * p, P.gamma)
+    check3(f"3d rho {rho:g} p {p:g}", P)
