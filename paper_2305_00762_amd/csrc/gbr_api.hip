@@ -843,7 +843,7 @@ static int batch_layout(gbr_batch* b) {
   ts[b->nprob] = (int)t;
   b->total = (int)t;
   const long long need = (t + 7) / 8 * 8;   // one workgroup per tile (rounded to 8)
-  if (v.loop) {
+  if (v.loop && t >= v.few_tiles) {
     const int per_cu = v.occ[b->precision == GBR_PREC_FP32_BULK ? 1 : 0]();
     if (per_cu < 1) return GBR_EDEVICE;
     long long g = (long long)per_cu * b->cus;
@@ -901,7 +901,9 @@ static void batch_launch_stage(gbr_batch* b, int x, int st, hipStream_t s) {
   B.tile_start = b->d_tile_start;
   B.nprob = b->nprob;
   B.total = b->total;
-  batch_variants()[b->tiling].fn[b->precision == GBR_PREC_FP32_BULK ? 1 : 0](B, b->grid, s);
+  const BatchVariant& v = batch_variants()[b->tiling];
+  const int prec = b->precision == GBR_PREC_FP32_BULK ? 1 : 0;
+  (b->total < v.few_tiles ? v.few : v.fn)[prec](B, b->grid, s);
 }
 
 // One SSP-RK3 step from array set x: stages into y, z, y (y = x+1, z = x+2

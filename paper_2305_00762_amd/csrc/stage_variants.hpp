@@ -43,6 +43,8 @@ struct BatchVariant {
   int tx, ty, loop;
   BatchLaunchFn fn[2];   // [FP64, FP32 bulk]
   int (*occ[2])();       // workgroups per CU
+  int few_tiles;         // batches of fewer tiles launch few, one workgroup per tile
+  BatchLaunchFn few[2];
 };
 constexpr int kNumBatchVariants = 4;
 const BatchVariant* batch_variants();
