@@ -177,7 +177,10 @@ int gbr_rk_stage(gbr_ctx *ctx, int stage, const double *dt_dev, const double *Qn
 /* The time step of Sec. 2.5:
  *   dt = cfl * min( (1/alpha_v) min(dx^2/nu, dy^2/nu), min(dx/(|u|+c), dy/(|v|+c)) )
  * over all cells of Q, alpha_v = 4, nu = mu/rho, c = sqrt(gamma p/rho);
- * written to the device double *dt_dev.  cfl > 0. */
+ * written to the device double *dt_dev.  cfl > 0.  The time-step calls of one
+ * context share scratch memory: order them on the device (one stream, or events).
+ * Up to eight calls of gbr_compute_dt, on grids of up to 40000 cells, may run at
+ * the same time; a captured call counts among them whenever its graph runs. */
 int gbr_compute_dt(gbr_ctx *ctx, const double *Q, double cfl, double *dt_dev,
                    void *stream);
 
@@ -469,7 +472,8 @@ int gbr3_rk_stage(gbr3_ctx *ctx, int stage, const double *dt_dev, const double *
                   const double *Qk, double *Qout, void *stream);
 
 /* dt = cfl min(dx/(|u|+c), dy/(|v|+c), dz/(|w|+c)) over the grid (Sec. 2.5,
- * inviscid), to a device scalar; deterministic. */
+ * inviscid), to a device scalar; deterministic.  Calls of one context that run at
+ * the same time: as for gbr_compute_dt. */
 int gbr3_compute_dt(gbr3_ctx *ctx, const double *Q, double cfl, double *dt_dev, void *stream);
 
 /* The same time step of the state the last stage-3 call wrote, from the

@@ -37,20 +37,25 @@ inline int dt_arrivals(size_t n) {
   return (int)(want < (size_t)kDtArrivals ? want : kDtArrivals);
 }
 
-// Scratch of the one-launch forms, in turn: kDtTurns sets for the step of a
-// state and as many for that of stage-3 extrema, so that calls of one context
-// that overlap on several streams do not meet in a count.  A set is kDtArrivals
-// slots of each row of the partial extrema and a word behind the status words.
+// Scratch of the one-launch forms: kDtTurns sets for the step of a state and as
+// many for that of stage-3 extrema, each class taken in its own turn, so up to
+// kDtTurns calls of a class may be under way at once (several streams).  A set is
+// kDtArrivals slots of each row of partial extrema, behind those of the two-launch
+// forms, and a word behind the status words.  Every launch of a set has the same
+// number of workgroups, a constant of the context: whatever calls meet in a set
+// (more than kDtTurns at once, or a replayed graph, which keeps the set it was
+// captured with), its count is back at zero when they are done.
 constexpr unsigned kDtTurns = 8;
 constexpr size_t kStatusWords = 16 + 2 * kDtTurns;
+constexpr size_t kDtPartials = 2 * 3 * (size_t)kDtBlocks;
 static_assert(2 * kDtTurns * kDtArrivals <= (unsigned)kDtBlocks, "sets fit the partials");
 struct DtSet {
   double* partial;
   unsigned* count;
 };
-inline DtSet dt_set(double* partial, unsigned* status, unsigned& turn, bool extrema) {
-  const unsigned k = (turn++ % kDtTurns) + (extrema ? kDtTurns : 0);
-  return {partial + k * kDtArrivals, status + 16 + k};
+inline DtSet dt_set(double* partial, unsigned* status, unsigned (&turn)[2], bool extrema) {
+  const unsigned k = turn[extrema]++ % kDtTurns + (extrema ? kDtTurns : 0);
+  return {partial + 3 * kDtBlocks + k * kDtArrivals, status + 16 + k};
 }
 
 struct DtParams {

@@ -25,7 +25,8 @@ __device__ __forceinline__ double block_min(double v, double* red) {
 // extremum m of two values, id[m] its identity.  An extremum is exact, so the
 // order of arrival does not show in the result.  Slots and count are written
 // and read at device scope (the XCDs' L2s hold no common copy of plain
-// accesses); atomicInc returns count to zero for the next launch.
+// accesses); atomicInc returns count to zero for the next launch, as every launch
+// on one count has the same number of workgroups.
 template <int NV, class Fold, class Fin>
 __device__ __forceinline__ void dt_commit(double (&v)[NV], const double (&id)[NV], double* partial,
                                           unsigned* count, Fold fold, Fin fin) {

@@ -35,8 +35,8 @@ struct gbr_ctx {
   int device;
   int export_flags;
   unsigned* d_status;         // [4] status, then the arrival counts (kStatusWords)
-  unsigned dt_turn = 0;       // next set of the one-launch time step
-  double* d_partial;          // [3][kDtBlocks] time-step partial extrema
+  unsigned dt_turn[2] = {0, 0};   // next set of the one-launch time step: states, extrema
+  double* d_partial;          // [kDtPartials] time-step partial extrema
   double* d_dtx;              // [3][slots] per-wave time-step extrema of a stage-3 output
   int dtx_cap;                // slots d_dtx holds (the most of any tile shape)
   int stage3_slots;           // slots of the last stage-3 call; 0: none since gbr_stage_dt
@@ -138,7 +138,7 @@ int gbr_init(int nx, int ny, double gamma, double mu, double Pr, gbr_ctx** out) 
   c->precision = GBR_PREC_FP64; c->detector = GBR_DET_PLAIN;
   if (hipGetDevice(&c->device) != hipSuccess) { delete c; return GBR_EDEVICE; }
   if (hipMalloc(&c->d_status, kStatusWords * sizeof(unsigned)) != hipSuccess) { delete c; return GBR_ENOMEM; }
-  if (hipMalloc(&c->d_partial, 3 * kDtBlocks * sizeof(double)) != hipSuccess) {
+  if (hipMalloc(&c->d_partial, kDtPartials * sizeof(double)) != hipSuccess) {
     (void)hipFree(c->d_status); delete c; return GBR_ENOMEM;
   }
   if (hipMalloc(&c->d_sides, 4 * sizeof(SideDev)) != hipSuccess) {
@@ -569,7 +569,8 @@ int gbr_stage_dt(gbr_ctx* c, double cfl, double* dt_dev, void* stream) {
   P.partial = set.partial; P.count = set.count;
   P.dt = dt_dev; P.status = c->d_status; P.cfl = cfl; P.mu = c->mu;
   P.dx = (c->x1 - c->x0) / c->nx; P.dy = (c->y1 - c->y0) / c->ny;
-  hipLaunchKernelGGL(dt_extrema_kernel<false>, dim3(dt_arrivals(P.nslot)), dim3(kDtThreads), 0,
+  // workgroups by the slots of the smallest tiles, whichever shape wrote these
+  hipLaunchKernelGGL(dt_extrema_kernel<false>, dim3(dt_arrivals(c->dtx_cap)), dim3(kDtThreads), 0,
                      s, P);
   c->stage3_slots = 0;
   c->rp_armed = c->rp_valid;
@@ -1166,8 +1167,8 @@ struct gbr3_ctx {
   int device;
   int export_flags;
   unsigned* d_status;         // [4] status, then the arrival counts (kStatusWords)
-  unsigned dt_turn = 0;       // next set of the one-launch time step
-  double* d_partial;          // [3][kDtBlocks]
+  unsigned dt_turn[2] = {0, 0};   // next set of the one-launch time step: states, extrema
+  double* d_partial;          // [kDtPartials]
   double* d_R;                // [5][nz][ny][nx] residual accumulator
   double* d_dtx;              // [3][slots] per-wave time-step extrema of a stage-3 output
   int stage3_slots;           // slots of the last stage-3 call; 0: none since gbr3_stage_dt
@@ -1191,7 +1192,7 @@ int gbr3_init(int nx, int ny, int nz, double gamma, gbr3_ctx** out) {
   const size_t zslots = (size_t)col3_tiles(nx, ny, nz) * kCol3Waves;
   bool ok = hipGetDevice(&c->device) == hipSuccess &&
             hipMalloc(&c->d_status, kStatusWords * sizeof(unsigned)) == hipSuccess &&
-            hipMalloc(&c->d_partial, 3 * kDtBlocks * sizeof(double)) == hipSuccess &&
+            hipMalloc(&c->d_partial, kDtPartials * sizeof(double)) == hipSuccess &&
             hipMalloc(&c->d_R, 5 * n * sizeof(double)) == hipSuccess &&
             hipMalloc(&c->d_dtx, 3 * zslots * sizeof(double)) == hipSuccess &&
             hipMemset(c->d_status, 0, kStatusWords * sizeof(unsigned)) == hipSuccess &&
