@@ -128,7 +128,7 @@ def parse():
     ap.add_argument("--calib-copy-mb", type=int, default=0,
                     help="run one device copy of this many MiB first (HBM counter calibration)")
     ap.add_argument("--sweeps3", default="lines", choices=sorted(SWEEPS3),
-                    help="3D launch form (one pair of kernels serves every value)")
+                    help="3D launch form: every value is accepted and runs the same pair of kernels")
     ap.add_argument("--tiling", default="auto",
                     help="tile variant index, or 'auto' (gbr_autotune on the initial state)")
     return ap.parse_args()
@@ -448,7 +448,7 @@ def tg_diagnostics(Q, dx):
 def bench_3d(a, n):
     """The paper's 3D case: inviscid Taylor-Green vortex, 64^3, t = 0..10, at
     the requested GRB order with the other order run beside it: whole-run time,
-    throughput, the sweep kernels' roofline, and the kinetic energy and
+    throughput, the stage kernels' roofline, and the kinetic energy and
     enstrophy histories (the paper's comparison of fourth- and seventh-order
     GRB)."""
     import numpy as np
@@ -511,7 +511,7 @@ def bench_3d(a, n):
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f64",
         "data": "synthetic",
         "config": {"workload": "taylor_green3d", "description": WORKLOADS["taylor_green3d"][4],
-                   "nx": n, "ny": n, "nz": n, "order": head_order, "sweeps": a.sweeps3,
+                   "nx": n, "ny": n, "nz": n, "order": head_order,
                    "step": step_3d(a)},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None,
@@ -618,7 +618,7 @@ def bench_3d_fixed(a, n, steps):
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f64",
         "data": "synthetic",
         "config": {"workload": a.workload, "description": WORKLOADS[a.workload][4],
-                   "nx": n, "ny": n, "nz": n, "order": 7, "sweeps": a.sweeps3,
+                   "nx": n, "ny": n, "nz": n, "order": 7,
                    "step": step_3d(a)},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None, "kernel": kernel_3d(a),

@@ -237,9 +237,10 @@ int gbr_timing_read(gbr_ctx *ctx, double *detector_ms, double *stage_ms, uint64_
 
 /* Tile shapes of the stage kernel (31x15, 15x15, 63x7, 30x15; small grids take
  * the 15x15 shape as 15x7 workgroups).
- * gbr_tiling_count() is the number of compiled shapes; gbr_set_tiling selects one (0 = default 31x15 cells per
- * workgroup); gbr_get_tiling reports the shape in use (the viscous form falls
- * back to variant 0 where a shape has no viscous build).  gbr_autotune times
+ * gbr_tiling_count() is the number of compiled shapes; gbr_set_tiling selects
+ * one (0 = default 31x15 cells per workgroup); gbr_get_tiling reports the shape
+ * in use (the viscous form falls back to variant 0 where a shape has no viscous
+ * build).  gbr_autotune times
  * every shape on the residual of the device state Q (reps launches each,
  * enqueued on `stream` and synchronised) and keeps the fastest; it allocates
  * and frees one scratch array of the size of Q. */
@@ -457,9 +458,9 @@ int gbr3_set_geometry(gbr3_ctx *ctx, double x0, double x1, double y0, double y1,
 int gbr3_set_order(gbr3_ctx *ctx, int order);
 
 /* Launch form of a residual or stage call.  Every value is accepted and served
- * by the same two kernels: the x and y lines of 15x15 tiles of each z plane
- * (residual accumulator written once), then the z lines.  GBR_EINVAL for
- * another value. */
+ * by the same two kernels: the x and y lines of tiles of each z plane (15x15,
+ * 16x16 or 20x17 cells, by the grid; residual accumulator written once), then the
+ * z lines.  GBR_EINVAL for another value. */
 enum { GBR3_SWEEPS_LINES = 0, GBR3_SWEEPS_XY_FUSED = 1, GBR3_SWEEPS_XY_FUSED_HALF = 2 };
 int gbr3_set_sweeps(gbr3_ctx *ctx, int form);
 
@@ -495,8 +496,8 @@ int gbr3_get_flags(gbr3_ctx *ctx, uint8_t *sig_x, uint8_t *sig_y, uint8_t *sig_z
 int gbr3_check(gbr3_ctx *ctx, void *stream);
 
 /* Timing of residual and stage calls: two HIP events per call on the caller's
- * stream; gbr3_timing_read returns the summed milliseconds of the three sweep
- * kernels and the number of calls, and resets. */
+ * stream; gbr3_timing_read returns the summed milliseconds of both kernels of
+ * the calls and the number of calls, and resets. */
 int gbr3_timing(gbr3_ctx *ctx, int enable);
 int gbr3_timing_read(gbr3_ctx *ctx, double *sweeps_ms, uint64_t *calls);
 

@@ -11,9 +11,9 @@
 // consecutive tiles go to one XCD (workgroup b runs on XCD b mod 8), so the
 // halo re-reads of neighbouring tiles meet in the same L2.  Each tile runs the
 // same tile function as the single-grid kernels (inviscid or viscous form,
-// chosen per grid), so a grid of the batch computes what a single-grid launch
-// with the same tile shape computes, up to how the compiler contracts
-// multiply-adds in the two kernels.  The time step is per grid: a
+// chosen per grid; multiply-adds fuse as the source groups them), so a grid of
+// the batch computes what a single-grid launch with the same tile shape and
+// interfaces per lane computes.  The time step is per grid: a
 // two-pass min-reduction with a fixed number of partials per grid.  Every
 // workgroup leaves the tile loop after at most ceil(total / gridDim.x)
 // rounds.

@@ -714,7 +714,7 @@ def gbr3_timing(ctx, enable):
 
 
 def gbr3_timing_read(ctx):
-    """(summed ms of the sweep kernels, calls) since timing was enabled or read."""
+    """(summed ms of both stage kernels, calls) since timing was enabled or read."""
     t, n = C.c_double(), C.c_uint64()
     _check(load().gbr3_timing_read(ctx, C.byref(t), C.byref(n)), "gbr3_timing_read")
     return t.value, n.value
