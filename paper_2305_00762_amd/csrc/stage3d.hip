@@ -12,7 +12,8 @@ namespace gbr {
 // 16x16 K = 3, 20x17 K = 3), octant Riemann fields: 128^3 168, 160, 151;
 // 96^3 80, 78, 74; 80^3 55, 55, 53; 75^3 44, 51, 49; 64^3 36, 31, 38;
 // 56^3 26, 30, 28; 32^3 16, 17, 18; Taylor-Green 64^3 23.0, 18.7, 20.0.
-// (15x15 K = 1: 179 at 128^3, 25 at Taylor-Green 64^3.)
+// (15x15 K = 1: 179 at 128^3, 25 at Taylor-Green 64^3.)  Taken before the Riemann
+// solver's two further estimates, which add 1%.
 constexpr long long kOneRound = 3 * 256;
 
 template <class C>

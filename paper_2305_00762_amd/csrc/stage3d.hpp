@@ -12,12 +12,15 @@
 //   column: kCol3W consecutive cells of the xy plane x 15 cells along z with the
 //          halo along z; adds -dH/dz and stores the residual or the SSP-RK3
 //          stage (eq. rk).
-// The plane kernel is bound by VALU issue (151 us on the octant Riemann field
-// of 128^3, where 14% of the interfaces take the shock branch; 158 with 15x15
-// tiles and two interfaces a lane), the column kernel by memory (92 us there
-// for the 200 B a cell-stage moves, 4.6 TB/s; 98 with 32 lines).  One
-// barrier-phased kernel per direction, with staged gradients and fluxes in
-// LDS, took 126 + 141 + 159 us on that field.
+// The octant Riemann field of 128^3, where 14% of the interfaces take the shock
+// branch, takes 151 us in the plane kernel (158 with 15x15 tiles and two interfaces
+// a lane) and 92 in the column kernel (98 with 32 lines); 163 and 105 on average
+// over a run.  Neither a unit nor memory is saturated there: VALU is busy 65% and
+// 61%, HBM traffic 161 and 324 MiB a launch (profiled: 177 and 119 us).  The plane
+// kernel's x sweep pays for its row stride of 32 doubles on 20x17 tiles: 4.5 bank
+// conflict cycles per LDS instruction, against 1.3 on the 16x16 tiles of 64^3.  One
+// barrier-phased kernel per direction, with staged gradients and fluxes in LDS,
+// took 126 + 141 + 159 us on that field.
 #pragma once
 #include "dt_kernel_common.hpp"
 #include "meg7_device.hpp"

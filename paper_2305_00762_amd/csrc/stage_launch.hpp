@@ -32,6 +32,7 @@ int launch_line_cfg(const StageParams& P, hipStream_t s) {
 //   600^2    31.6 28.8 30.5   38.1 33.2       (1600, 800)
 //   700^2    40.6 36.1 34.8   50.6 36.4       40.7 30.7 31.1   46.2 30.3   (2209, 1081)
 //   1024^2   76.0 64.2 56.6   93.9 59.5       79.8 59.3 54.1   89.9 53.3
+// (taken before the Riemann solver's two further estimates, which add 1 to 2%).
 // MEG7-cons needs more registers than four waves per SIMD leave, so its K = 1
 // ends earlier (K = 1, 2; 15x15): 128^2 16.4 19.1, 256^2 21.8 23.7 (324 tiles),
 // 400^2 35.2 28.9.

@@ -23,14 +23,17 @@
 // central one in float32.  The mean flux, MP limiter, viscous flux and
 // divergence are FP64.
 //
-// What bounds it: VALU issue, busy 83% at 4096^2 (15x15 tiles, K = 4; 86% on
-// 31x15, FP32 94 and 95%).  The barrier-phased form with per-line buffers before
-// it issued 1.2 times the VALU and 2.8 times the LDS instructions, whose waits
-// held it at 57%.  The 48 running sums of K = 4 fit 168 registers, 3 waves per
-// SIMD; K = 8 does not.
-// Measured per stage (Riemann field, that form -> this): 4096^2 FP64 1071 ->
-// 678 us (15x15), 663 (31x15), FP32 803 -> 619; 1024^2 FP64 91 -> 57; viscous
-// shear 2048^2 FP64 303 -> 192, FP32 235 -> 177.  Unphysical smooth states go
+// What bounds it: VALU issue on large grids (busy 83 to 88% at 4096^2 on 30x15
+// tiles, 85% on the viscous 2048^2 field, K = 4); with few rounds of tiles also
+// their tail and each wave's chain (1024^2 74%, 1283x719 viscous 75%, double Mach
+// 1024x256 63%, 64^2 19%).  The barrier-phased form with per-line buffers before it
+// issued 1.2 times the VALU and 2.8 times the LDS instructions, whose waits held
+// it at 57%.  The 48 running sums of K = 4 fit 168 registers, 3 waves per SIMD;
+// K = 8 does not.
+// Measured per stage (events; that form -> this): Riemann 4096^2 15x15 FP64 1087
+// -> 679 us, FP32 763 -> 617, 31x15 FP64 1259 -> 642; 1024^2 15x15 FP64 87 -> 62;
+// viscous shear 2048^2 15x15 FP64 341 -> 239, FP32 251 -> 218, 31x15 406 -> 224,
+// 333 -> 209; MEG7-cons tube 1280x640 83 -> 64.  Unphysical smooth states go
 // through the same per-wave queue as flagged interfaces (kFirstOrder): their
 // first-order fallback inline held registers and split every interface in
 // blocks; a step of the 1280x640 MEG7-cons tube took 212 us with it, 193
