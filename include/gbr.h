@@ -18,7 +18,9 @@
  *     time; contexts are independent.
  *   - Device faults cannot be reported asynchronously: gbr_check()
  *     synchronises the stream and reports GBR_ESTATE if a kernel saw a
- *     non-finite value or a non-positive density or pressure.
+ *     non-finite value or a non-positive density or pressure.  What a call that
+ *     is reported so writes at cells whose stencils reach such a cell is not
+ *     specified.
  */
 #ifndef GBR_H
 #define GBR_H
