@@ -407,7 +407,8 @@ int gbr_batch_use_graph(gbr_batch *b, int enable);
 
 /* Launch forms: 0 = 31x15 and 1 = 15x15 cells per workgroup with a
  * persistent tile loop (as many workgroups as fit on the chip at once), 2 =
- * 31x15 and 3 = 15x15 with one workgroup per tile.  gbr_batch_autotune times
+ * 31x15 and 3 = 15x15 with one workgroup per tile (below 2200 tiles of 15x15 form
+ * 1 launches one workgroup per tile too).  gbr_batch_autotune times
  * the first stage of a step from the current state for each form (`reps`
  * launches, writing into the next array set, which a step overwrites anyway)
  * and keeps the fastest.  gbr_batch_info reports the form, its tile shape,
